@@ -240,14 +240,20 @@ pj_status pj_mech_get_arrhenius(const pj_mech* mech, double* lnA, double* b, dou
  * once (a power of two up to 64) with waves_per_group waves (1 to 8); 1 state
  * per workgroup is the paper's deep mapping (Sec. 2.1: the lanes of a
  * workgroup cooperate on one state), 64 states on one wave its shallow
- * mapping (a lane per state).  0 restores the automatic choice (the most
- * states, up to 4, whose working set fits the LDS of one workgroup, and
- * enough waves for about 8 resident waves per compute unit).  A
+ * mapping (a lane per state).  0 restores the automatic choice, which
+ * depends on the call's states and layout: few states and, for Jacobians,
+ * mechanisms of more than 256 reactions take one or two states per workgroup;
+ * the others the most states, up to 4, whose working set fits the LDS of one
+ * workgroup, and enough waves for about 8 resident waves per compute unit.  A
  * states_per_group that does not fit for a mode is ignored for that mode.
- * With one wave per workgroup every accumulation happens in a fixed order,
- * so results are bitwise reproducible; with more, the order of LDS atomic
- * additions across waves may vary between runs (results then agree to
- * rounding).  pj_mech_set_waves_per_state(w) is pj_mech_set_launch(1, w)
+ * One or two states with at least 2 waves (a multiple of the states, and for
+ * Jacobians one for every 320 reactions of a state) run kernels that add in a
+ * fixed order, without atomics, unless the mechanism was loaded for the
+ * run-time slot search or the fixed-order additions.
+ * With one wave per workgroup every accumulation happens in a fixed order
+ * too, so results are bitwise reproducible; with more (and 4 or more states),
+ * the order of LDS atomic additions across waves may vary between runs
+ * (results then agree to rounding).  pj_mech_set_waves_per_state(w) is pj_mech_set_launch(1, w)
  * (w in 1, 2, 4; 0 = automatic).
  */
 pj_status pj_mech_set_launch(pj_mech* mech, int states_per_group, int waves_per_group);
@@ -255,7 +261,8 @@ pj_status pj_mech_set_waves_per_state(pj_mech* mech, int waves_per_state);
 /* waves per workgroup when one state per workgroup is used, else -1 */
 int pj_mech_waves_per_state(const pj_mech* mech, int for_jacobian);
 /* launch shape of mode 0 (source), 1 (sparse Jacobian), 2 (dense Jacobian) or
- * 3 (adjoint, at most 4 states per workgroup); -1 on error */
+ * 3 (adjoint, at most 4 states per workgroup), of a large call in layout C
+ * where the choice is automatic; -1 on error */
 int pj_mech_launch_shape(const pj_mech* mech, int mode, int* states_per_group, int* waves_per_group);
 
 /*

@@ -46,6 +46,74 @@ int max_states(int kmode) {
 
 namespace pj {
 
+static int gather_mode(int mode) { return mode == MODE_SRC ? GM_SRC : mode == MODE_DENSE ? GM_DENSE : GM_JAC; }
+
+// A call with S states and w waves per workgroup runs on the gather kernels
+// (gather_body.h) if they are built for it: at most two states, each with a
+// wave of its own or more, a wave's reactions in at most GATHER_BLOCKS blocks
+// of 64.  One wave per workgroup stays with the scatter kernels (their fixed
+// order is documented), and so do the run-time slot search and the fixed-order
+// option, whose results are theirs by definition.  A dense Jacobian in layout
+// F is written by columns of single states at S = 1: 2993 us against the
+// scatter kernels' 2760 for 2048 states of 360 species.  The grid's threads
+// stay below 2^32.
+static bool gather_takes(const Mechanism& m, int mode, pj_layout layout, int64_t n, int S, int w) {
+    if (!m.gm.ok || m.dm.lsearch || m.dm.det || mode > MODE_DENSE) return false;
+    if (S > 2 || w < 2 || w % S) return false;
+    if (mode == MODE_DENSE && layout == PJ_LAYOUT_F && S == 1) return false;
+    if (mode != MODE_SRC && (m.nr + 63) / 64 > GATHER_BLOCKS * (w / S)) return false;
+    if ((n / S + 8) * 64 * w >= (int64_t)1 << 32) return false;
+    return gather_lds(m.gm, gather_mode(mode), S) <= m.lds_max;
+}
+
+// The automatic choice between the gather and the scatter kernels for a call
+// of n states, and the gather kernels' shape (false: scatter, in the shape of
+// choose_launch).  Measured on MI355X, scatter -> gather, us per call:
+//   few states: a workgroup per state or two fills the chip sooner; 13 species,
+//     1024 states, sparse 19.5 -> 14.7 (2048: 20.0 -> 18.3, 4096: 20.8 -> 36);
+//     53 species, 100 states, source terms 57 -> 10, sparse 67 -> 16.5;
+//     111 species, 4096 states, source terms 59 -> 34
+//   more than 256 reactions, Jacobians: 53 species, 71199 states, sparse
+//     1388 -> 1195 (layout F 1375 -> 1338), dense (17799) 408 -> 375; 111 species,
+//     16232 states 752 -> 650 (F 805 -> 764); 360 species, 4096 states 767 -> 682
+//     (F 1270 -> 848)
+//   fewer: 20 species, 131072 states, sparse 996 -> 1159
+static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_t n, int& S, int& w) {
+    if (mode > MODE_DENSE) return false;
+    const int blocks = (m.nr + 63) / 64;
+    const bool few = n <= 2048;
+    auto take = [&](int s, int v) {
+        if (!gather_takes(m, mode, layout, n, s, v)) return false;
+        S = s;
+        w = v;
+        return true;
+    };
+    if (mode == MODE_SRC) {
+        if (n <= 1024) return take(1, 4);
+        return n <= 4096 && blocks >= 2 && take(2, blocks <= 6 ? 2 : 4);
+    }
+    if (!few && blocks <= 4) return false;
+    // layout F: two states write twice as long runs; one if two leave a compute
+    // unit a single workgroup
+    if (layout == PJ_LAYOUT_F) {
+        if ((mode == MODE_DENSE || 2 * gather_lds(m.gm, GM_JAC, 2) <= m.lds_max) && take(2, blocks <= 2 * GATHER_BLOCKS ? 4 : 8))
+            return true;
+    } else if (!few && blocks <= 8 && take(2, 4)) {
+        return true;
+    }
+    return take(1, blocks <= 4 ? 2 : blocks <= 4 * GATHER_BLOCKS ? 4 : 8);
+}
+
+// the shape of a large call in layout C
+static void nominal_shape(const Mechanism& m, int mode, int& S, int& w, int64_t& lds) {
+    S = m.S[mode];
+    w = m.waves[mode];
+    lds = m.lds[mode];
+    const int64_t n = 1 << 20;
+    if (m.automatic[mode] ? gather_choice(m, mode, PJ_LAYOUT_C, n, S, w) : gather_takes(m, mode, PJ_LAYOUT_C, n, S, w))
+        lds = gather_lds(m.gm, gather_mode(mode), S);
+}
+
 // Waves per workgroup for S states per workgroup: enough that a compute unit
 // holds about 8 resident waves given how many workgroups fit in its LDS, and
 // at least S/64 so that every state has a lane.
@@ -80,6 +148,7 @@ void choose_launch(Mechanism& m) {
         m.S[mode] = S;
         m.waves[mode] = w;
         m.lds[mode] = L(S, w);
+        m.automatic[mode] = !m.user_S && !m.user_waves;
     }
 }
 
@@ -110,6 +179,14 @@ pj_status eval(const pj_mech* mech, int mode, pj_form form, pj_layout layout, in
     if (lds > m.lds_max)
         return fail(PJ_E_UNSUPPORTED, "per-state working set (" + std::to_string(lds) +
                                           " B) exceeds the LDS of one workgroup");
+    int gS = m.S[mode], gw = m.waves[mode];
+    if (m.automatic[mode] ? pj::gather_choice(m, mode, layout, n, gS, gw) : pj::gather_takes(m, mode, layout, n, gS, gw)) {
+        hipError_t e = pj::launch_gather({&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, gS, gw, n, state, param,
+                                          dstate, jac, arr, (hipStream_t)stream});
+        if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
+        g_err.clear();
+        return PJ_OK;
+    }
     // the hot loop of the static map carries no trace of the run-time search,
     // the fixed-order additions or per-call parameters: kernels of their own
     const int kmode = kernel_mode(m, mode, arr != nullptr);
@@ -295,6 +372,18 @@ pj_status pj_mech_set_arrhenius(pj_mech* mech, const double* lnA, const double* 
         hipError_t e = hipMemcpy((unsigned char*)m.dbuf + m.off_rec, m.h_rec.data(),
                                  m.h_rec.size() * sizeof(pj::RxnRec), hipMemcpyHostToDevice);
         if (cur >= 0 && cur != m.device) (void)hipSetDevice(cur);
+        if (e == hipSuccess && m.gm.ok) {
+            for (int p = 0; p < m.nr; ++p) {
+                const auto& r = m.rx[m.gorder[p]];
+                m.h_frec[p].lnA = r.lnA;
+                m.h_frec[p].b = r.b;
+                m.h_frec[p].theta = r.theta;
+            }
+            if (cur != m.device) (void)hipSetDevice(m.device);
+            e = hipMemcpy((unsigned char*)m.dbuf + m.off_frec, m.h_frec.data(), m.h_frec.size() * sizeof(pj::FastRec),
+                          hipMemcpyHostToDevice);
+            if (cur >= 0 && cur != m.device) (void)hipSetDevice(cur);
+        }
         if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("update of the reaction table failed: ") + hipGetErrorString(e));
     }
     g_err.clear();
@@ -343,7 +432,10 @@ pj_status pj_mech_set_waves_per_state(pj_mech* mech, int waves_per_state) {
 int pj_mech_waves_per_state(const pj_mech* mech, int for_jacobian) {
     if (!mech) return -1;
     const int mode = for_jacobian ? pj::MODE_SPARSE : pj::MODE_SRC;
-    return mech->m.S[mode] == 1 ? mech->m.waves[mode] : -1;
+    int S, w;
+    int64_t lds;
+    pj::nominal_shape(mech->m, mode, S, w, lds);
+    return S == 1 ? w : -1;
 }
 
 pj_status pj_mech_set_dense_unroll(pj_mech* mech, int entries) {
@@ -359,8 +451,11 @@ int pj_mech_dense_unroll(const pj_mech* mech) { return mech ? mech->m.dense_unro
 
 int pj_mech_launch_shape(const pj_mech* mech, int mode, int* states_per_group, int* waves_per_group) {
     if (!mech || mode < 0 || mode >= pj::N_MODES) return -1;
-    if (states_per_group) *states_per_group = mech->m.S[mode];
-    if (waves_per_group) *waves_per_group = mech->m.waves[mode];
+    int S, w;
+    int64_t lds;
+    pj::nominal_shape(mech->m, mode, S, w, lds);
+    if (states_per_group) *states_per_group = S;
+    if (waves_per_group) *waves_per_group = w;
     return 0;
 }
 
@@ -401,8 +496,13 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
             const int kmode = n_du == 2 ? (du == 16 ? pj::MODE_DENSE_U16 : pj::MODE_DENSE) : kmode0;
             if (kmode == pj::MODE_DENSE_U16 && S > 4) continue;   // built for at most 4 states
             const int64_t l = pj::lds_bytes(m.dm, mode, S, wv, gr);
-            if (l > m.lds_max) continue;
+            // a shape that the gather kernels take is theirs (timed once)
+            const bool gather = pj::gather_takes(m, mode, layout, n_states, S, wv);
+            if (l > m.lds_max || (gather && du != 16)) continue;
             auto go = [&]() {
+                if (gather)
+                    return pj::launch_gather({&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, S, wv, n_states,
+                                              d_state, d_param, dst, jac, nullptr, hs});
                 return pj::launch(m.dm, kmode, form, layout, S, n_states, d_state, d_param, dst, jac, vin, grad,
                                   gr ? 1 : 0, wv, l, hs);
             };
@@ -429,6 +529,7 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (!err.empty()) return fail(PJ_E_DEVICE, err);
+    m.automatic[mode] = false;
     m.S[mode] = best_S;
     m.waves[mode] = best_w;
     m.lds[mode] = pj::lds_bytes(m.dm, mode, best_S, best_w, gr);
@@ -467,7 +568,10 @@ pj_status pj_mech_autotune_adjoint(pj_mech* mech, pj_form form, pj_layout layout
 
 int64_t pj_mech_lds_bytes(const pj_mech* mech, int for_jacobian) {
     if (!mech) return -1;
-    return for_jacobian ? mech->m.lds[pj::MODE_SPARSE] : mech->m.lds[pj::MODE_SRC];
+    int S, w;
+    int64_t lds;
+    pj::nominal_shape(mech->m, for_jacobian ? pj::MODE_SPARSE : pj::MODE_SRC, S, w, lds);
+    return lds;
 }
 
 const char* pj_last_error(void) { return g_err.c_str(); }

@@ -156,6 +156,97 @@ struct DevMech {
                               // Ea/R (nr)] in description order, in place of the tables
 };
 
+// ---------------------------------------------------------------------------
+// Gather kernels (gather_body.h).  Each reaction writes the few numbers that
+// everything else is a sum of into a pool in LDS; production rates, Jacobian
+// rows and columns are then gathered from the pool through static lists, one
+// lane (or a power of two of lanes) per sum.
+
+// Per-reaction record.  Slots hold single molecules: a coefficient of 2 takes
+// two slots, so that every slot has coefficient 1 (at most three a side).
+struct alignas(16) FastRec {         // 64 B
+    uint32_t info;                   // GI_*
+    uint32_t pad;
+    uint32_t chunk;                  // as RxnRec::chunk, of the single-molecule slots
+    uint16_t sp[6];                  // species of slot a (Ns = empty)
+    uint16_t bpos;                   // pool element of the reverse rate (reversible)
+    uint16_t tpos;                   // first pool element of the third-body terms
+    uint16_t tab;                    // P-Log / Chebyshev: index of the TabRec
+    uint16_t qbpos;                  // pool element of the bath-gas partial
+    double lnA, b, theta, domega;    // as RxnRec
+};
+struct alignas(16) FastEff {         // 96 B; record 0 is all-empty
+    uint16_t sp[MAXEFF];             // species (Ns = unused entry)
+    double am1[MAXEFF];              // efficiency - 1
+    double bam1;                     // the bath gas's
+    double pad;
+};
+static_assert(sizeof(FastRec) == 64 && sizeof(FastEff) == 96, "record sizes");
+// bits of FastRec::info: kind 0..2, reversible 3, depends on the bath gas 4,
+// chemically activated 5, dnu + 3 in 8..10, molecules of each side in 12..13
+// and 14..15, slots that hold the bath gas in 16..21, third bodies in 24..27
+// (FastRec::chunk) a reaction of the chunk depends on the pressure or a third body
+constexpr uint32_t CHUNK_PRESSURE = 1u << 15;
+constexpr uint32_t GI_REV = 1u << 3, GI_BATH = 1u << 4, GI_CHEMACT = 1u << 5;
+
+// A set of sums whose lists are cut into groups of 64 lanes.  Every lane has
+// three words of contributions in its head and four in its ext, both found
+// from the group's index alone (loads that nothing waits for), and more in
+// chunks of four words.  A sum takes 2^k neighbouring lanes, the same for all
+// sums of a group.
+struct SumLists {
+    int n;                           // groups
+    int pad;
+    const PJ_GLOBAL uint2* desc;     // [n] {k | further chunks << 8, first further chunk}
+    const PJ_GLOBAL uint4* head;     // [n][64] {what the sum is, contributions}
+    const PJ_GLOBAL uint4* ext;      // [n][64]
+    const PJ_GLOBAL uint4* more;     // [chunks][64]
+};
+
+// One round of the Jacobian's species rows: the rows whose entries fit the
+// output buffer in LDS together.
+struct JacRound {                    // 48 B
+    int row0, row1;                  // rows [row0, row1) of the Jacobian
+    int e0, ne;                      // their CSR entries [e0, e0 + ne)
+    int heavy0, heavy1;              // groups of sums with many contributions
+    int mid0, mid1;                  // groups of at most 6
+    int light0, light1;              // pairs of groups of at most 2
+    int pad[2];
+};
+
+struct GatherMech {
+    int ns, nr, N, nnz, bath, n_dense_rows, approx, ok;
+    // pool elements: forward rates [0, nr), reverse rates, third-body terms,
+    // bath-gas partials, a zero; from b3 {dq/dT, dq/dS} of every reaction and of
+    // an empty one, then in their place q of each and dE of each, then the
+    // output buffer
+    int zero, b3, npool;
+    int n_rounds, pad;
+    int neff;                        // reactions p < neff have the FastEff p + 1, the others 0
+    int dshift;                      // entry word: position | column << 16 | dense row + 1 << dshift
+    const PJ_GLOBAL ThermoRec* th;
+    const PJ_GLOBAL double* tmid;
+    const PJ_GLOBAL double* wfac;
+    const PJ_GLOBAL FastRec* rec;
+    const PJ_GLOBAL FastEff* eff;
+    const PJ_GLOBAL FallRec* fall;
+    const PJ_GLOBAL TabRec* tab;
+    const PJ_GLOBAL double* tabd;
+    const PJ_GLOBAL int32_t* orig;
+    const PJ_GLOBAL int32_t* row_ptr;
+    const PJ_GLOBAL uint16_t* ccs_pos;
+    const PJ_GLOBAL uint16_t* dmap_rm;
+    SumLists sl;                     // species: reactions (p | minus << 15)
+    SumLists bl;                     // bath-dense rows: their bath-gas partials
+    SumLists cl;                     // columns: (pool element << 3 | minus) | reaction << 16 | dOmega << 29
+    SumLists jh;                     // species rows, many contributions
+    const PJ_GLOBAL uint4* jm;       // [groups][64] {entry, 6 contributions}
+    const PJ_GLOBAL uint4* jl;       // [pairs][64] {entry, 2 contributions} of two groups
+    const PJ_GLOBAL JacRound* rounds;
+};
+constexpr int GATHER_BLOCKS = 5;     // most 64-reaction blocks of a wave
+enum GatherMode : int { GM_SRC = 0, GM_JAC = 1, GM_DENSE = 2 };
+
 struct Mechanism {
     // host copy of the description
     int ns = 0, nr = 0;
@@ -201,6 +292,14 @@ struct Mechanism {
     size_t off_rec = 0;
     int user_S = 0, user_waves = 0;        // 0 = automatic
     int dense_unroll = 16;                 // dense output: map entries in flight per lane (8 or 16)
+    bool automatic[4] = {}; // the mode's launch shape is the automatic one
+    // gather kernels: tables and the host copy of the reaction records with its
+    // byte offset (Arrhenius parameters)
+    GatherMech gm{};
+    const GatherMech* d_gm = nullptr;      // its device copy
+    std::vector<FastRec> h_frec;
+    std::vector<int32_t> gorder;           // their kernel position -> description index
+    size_t off_frec = 0;
     int lds_max = 0;
 };
 
@@ -228,6 +327,41 @@ constexpr int BATCH_MAX_S = 16;
 // mech.cpp
 pj_status build_mechanism(const char* path, Mechanism& m, std::string& err);
 pj_status upload_mechanism(Mechanism& m, std::string& err);
+
+// gather.cpp: the gather kernels' tables of a parsed mechanism, appended to
+// the host image of the device buffer (offsets relative to it) and, once the
+// buffer exists, their addresses
+struct GatherImage {
+    bool ok = false;
+    GatherMech gm{};
+    std::vector<int32_t> order;            // kernel position -> description index
+    std::vector<FastRec> rec;
+    std::vector<FallRec> fall;
+    std::vector<FastEff> eff;
+    struct Lists {
+        std::vector<uint2> desc;
+        std::vector<uint4> head, ext, more;
+    } sl, bl, cl, jh;
+    std::vector<uint4> jm, jl;
+    std::vector<JacRound> rounds;
+};
+void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std::vector<FallRec>& fall,
+                  const std::vector<int32_t>& dense_rows,
+                  int64_t lds_max, GatherImage& g);
+// gather.hip, gather_ext.hip (gather_body.h)
+int64_t gather_lds(const GatherMech& gm, int gmode, int S);
+struct GatherCall {
+    const GatherMech* gm;            // host copy: sizes for the launch
+    const GatherMech* d_gm;          // device copy
+    int ext, gmode, form, layout, S, waves;
+    int64_t n;
+    const double *state, *param;
+    double *dstate, *jac;
+    const double* arr;               // as DevMech::arr
+    hipStream_t stream;
+};
+hipError_t launch_gather(const GatherCall& c);
+hipError_t launch_gather_ext(const GatherCall& c);
 
 // kernels.hip (kernel_body.h)
 enum Mode : int { MODE_SRC = 0, MODE_SPARSE = 1, MODE_DENSE = 2, MODE_ADJ = 3,

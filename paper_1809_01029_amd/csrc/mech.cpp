@@ -569,6 +569,28 @@ pj_status upload_mechanism(Mechanism& m, std::string& err) {
     for (int j = 0; j < N; ++j) dmcm[(size_t)N * j] = dmcm[1 + (size_t)N * j] = DMAP_SKIP;
     size_t o_rowof = place(row16.size() * 2), o_orig = place(orig.size() * 4), o_ccs = place(ccs.size() * 2);
     size_t o_dmrm = place(dmrm.size() * 2), o_dmcm = place(dmcm.size() * 2);
+
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) { err = "no HIP device"; return PJ_E_DEVICE; }
+    int lds_max = 0;
+    if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
+        lds_max = 65536;
+    // the gather kernels' tables
+    GatherImage gi;
+    build_gather(m, rec, fall, n_dense ? dense_rows : std::vector<int32_t>{}, lds_max, gi);
+    auto vbytes = [](const auto& v) { return std::max<size_t>(1, v.size()) * sizeof(v[0]); };
+    size_t o_frec = place(vbytes(gi.rec)), o_feff = place(vbytes(gi.eff)), o_ffall = place(vbytes(gi.fall)),
+           o_gorig = place(vbytes(gi.order));
+    size_t o_list[4][4];
+    const GatherImage::Lists* const gl[4] = {&gi.sl, &gi.bl, &gi.cl, &gi.jh};
+    for (int q = 0; q < 4; ++q) {
+        o_list[q][0] = place(vbytes(gl[q]->desc));
+        o_list[q][1] = place(vbytes(gl[q]->head));
+        o_list[q][2] = place(vbytes(gl[q]->ext));
+        o_list[q][3] = place(vbytes(gl[q]->more));
+    }
+    size_t o_jm = place(vbytes(gi.jm)), o_jl = place(vbytes(gi.jl)), o_rounds = place(vbytes(gi.rounds)),
+           o_gm = place(sizeof(GatherMech));
     std::vector<unsigned char> host(total, 0);
     auto put = [&](size_t off, const void* src, size_t bytes) { std::memcpy(host.data() + off, src, bytes); };
     put(o_th, th.data(), th.size() * sizeof(ThermoRec));
@@ -588,11 +610,51 @@ pj_status upload_mechanism(Mechanism& m, std::string& err) {
     put(o_ccs, ccs.data(), ccs.size() * 2);
     put(o_dmrm, dmrm.data(), dmrm.size() * 2);
     put(o_dmcm, dmcm.data(), dmcm.size() * 2);
+    auto putv = [&](size_t off, const auto& v) { if (!v.empty()) put(off, v.data(), v.size() * sizeof(v[0])); };
+    putv(o_frec, gi.rec);
+    putv(o_feff, gi.eff);
+    putv(o_ffall, gi.fall);
+    putv(o_gorig, gi.order);
+    for (int q = 0; q < 4; ++q) {
+        putv(o_list[q][0], gl[q]->desc);
+        putv(o_list[q][1], gl[q]->head);
+        putv(o_list[q][2], gl[q]->ext);
+        putv(o_list[q][3], gl[q]->more);
+    }
+    putv(o_jm, gi.jm);
+    putv(o_jl, gi.jl);
+    putv(o_rounds, gi.rounds);
 
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess) { err = "no HIP device"; return PJ_E_DEVICE; }
     void* d = nullptr;
     if (hipMalloc(&d, total) != hipSuccess) { err = "hipMalloc of the mechanism tables failed"; return PJ_E_DEVICE; }
+    auto P = [&](size_t off) { return (const void*)((const unsigned char*)d + off); };
+    GatherMech& gm = m.gm;
+    gm = gi.gm;
+    gm.th = gptr((const ThermoRec*)P(o_th));
+    gm.tmid = gptr((const double*)P(o_tmid));
+    gm.wfac = gptr((const double*)P(o_wfac));
+    gm.rec = gptr((const FastRec*)P(o_frec));
+    gm.eff = gptr((const FastEff*)P(o_feff));
+    gm.fall = gptr((const FallRec*)P(o_ffall));
+    gm.tab = gptr((const TabRec*)P(o_tab));
+    gm.tabd = gptr((const double*)P(o_tabd));
+    gm.orig = gptr((const int32_t*)P(o_gorig));
+    gm.row_ptr = gptr((const int32_t*)P(o_rowp));
+    gm.ccs_pos = (m.opts & PJ_OPT_CCS) ? gptr((const uint16_t*)P(o_ccs)) : nullptr;
+    gm.dmap_rm = gptr((const uint16_t*)P(o_dmrm));
+    SumLists* const dl[4] = {&gm.sl, &gm.bl, &gm.cl, &gm.jh};
+    for (int q = 0; q < 4; ++q) {
+        dl[q]->n = (int)gl[q]->desc.size();
+        dl[q]->desc = gptr((const uint2*)P(o_list[q][0]));
+        dl[q]->head = gptr((const uint4*)P(o_list[q][1]));
+        dl[q]->ext = gptr((const uint4*)P(o_list[q][2]));
+        dl[q]->more = gptr((const uint4*)P(o_list[q][3]));
+    }
+    gm.jm = gptr((const uint4*)P(o_jm));
+    gm.jl = gptr((const uint4*)P(o_jl));
+    gm.rounds = gptr((const JacRound*)P(o_rounds));
+    put(o_gm, &gm, sizeof(gm));
+    m.d_gm = (const GatherMech*)P(o_gm);
     if (hipMemcpy(d, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) {
         (void)hipFree(d);
         err = "copy of the mechanism tables failed";
@@ -600,7 +662,6 @@ pj_status upload_mechanism(Mechanism& m, std::string& err) {
     }
     m.device = dev;
     m.dbuf = d;
-    auto P = [&](size_t off) { return (const void*)((const unsigned char*)d + off); };
     DevMech& dm = m.dm;
     dm.ns = ns;
     dm.nr = nr;
@@ -636,9 +697,9 @@ pj_status upload_mechanism(Mechanism& m, std::string& err) {
     m.h_rec = rec;
     m.off_rec = o_rec;
 
-    int lds_max = 0;
-    if (hipDeviceGetAttribute(&lds_max, hipDeviceAttributeMaxSharedMemoryPerBlock, dev) != hipSuccess)
-        lds_max = 65536;
+    m.h_frec = gi.rec;
+    m.gorder = gi.order;
+    m.off_frec = o_frec;
     m.lds_max = lds_max;
     if (lds_bytes(dm, MODE_SRC, 1, 1) > lds_max) {
         err = "source-term working set exceeds the LDS of one workgroup";
