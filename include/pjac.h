@@ -249,7 +249,9 @@ pj_status pj_mech_get_arrhenius(const pj_mech* mech, double* lnA, double* b, dou
  * One or two states with at least 2 waves (a multiple of the states, and for
  * Jacobians one for every 320 reactions of a state) run kernels that add in a
  * fixed order, without atomics, unless the mechanism was loaded for the
- * run-time slot search or the fixed-order additions.
+ * run-time slot search or the fixed-order additions.  So does the adjoint with
+ * one state (without fused source terms); its parameter sums are added over
+ * the workgroups in any order.
  * With one wave per workgroup every accumulation happens in a fixed order
  * too, so results are bitwise reproducible; with more (and 4 or more states),
  * the order of LDS atomic additions across waves may vary between runs

@@ -46,11 +46,11 @@ int max_states(int kmode) {
 
 namespace pj {
 
-static int gather_mode(int mode) { return mode == MODE_SRC ? GM_SRC : mode == MODE_DENSE ? GM_DENSE : GM_JAC; }
+static int gather_mode(int mode) { return mode == MODE_SRC ? GM_SRC : mode == MODE_ADJ ? GM_ADJ : mode == MODE_DENSE ? GM_DENSE : GM_JAC; }
 
 // A call with S states and w waves per workgroup runs on the gather kernels
-// (gather_body.h) if they are built for it: at most two states, each with a
-// wave of its own or more, a wave's reactions in at most GATHER_BLOCKS blocks
+// (gather_body.h) if they are built for it: at most two states (the adjoint
+// one), each with a wave of its own or more, a wave's reactions in at most GATHER_BLOCKS blocks
 // of 64.  One wave per workgroup stays with the scatter kernels (their fixed
 // order is documented), and so do the run-time slot search and the fixed-order
 // option, whose results are theirs by definition.  A dense Jacobian in layout
@@ -58,10 +58,10 @@ static int gather_mode(int mode) { return mode == MODE_SRC ? GM_SRC : mode == MO
 // scatter kernels' 2760 for 2048 states of 360 species.  The grid's threads
 // stay below 2^32.
 static bool gather_takes(const Mechanism& m, int mode, pj_layout layout, int64_t n, int S, int w) {
-    if (!m.gm.ok || m.dm.lsearch || m.dm.det || mode > MODE_DENSE) return false;
-    if (S > 2 || w < 2 || w % S) return false;
+    if (!m.gm.ok || m.dm.lsearch || m.dm.det) return false;
+    if (S > (mode == MODE_ADJ ? 1 : 2) || w < 2 || w % S) return false;
     if (mode == MODE_DENSE && layout == PJ_LAYOUT_F && S == 1) return false;
-    if (mode != MODE_SRC && (m.nr + 63) / 64 > GATHER_BLOCKS * (w / S)) return false;
+    if ((mode == MODE_SPARSE || mode == MODE_DENSE) && (m.nr + 63) / 64 > GATHER_BLOCKS * (w / S)) return false;
     if ((n / S + 8) * 64 * w >= (int64_t)1 << 32) return false;
     return gather_lds(m.gm, gather_mode(mode), S) <= m.lds_max;
 }
@@ -79,7 +79,6 @@ static bool gather_takes(const Mechanism& m, int mode, pj_layout layout, int64_t
 //     (F 1270 -> 848)
 //   fewer: 20 species, 131072 states, sparse 996 -> 1159
 static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_t n, int& S, int& w) {
-    if (mode > MODE_DENSE) return false;
     const int blocks = (m.nr + 63) / 64;
     const bool few = n <= 2048;
     auto take = [&](int s, int v) {
@@ -88,6 +87,22 @@ static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_
         w = v;
         return true;
     };
+    if (mode == MODE_ADJ) {
+        // Few states: a workgroup each.  Then the workgroups' additions of their
+        // parameter sums to the output weigh (about 50 ps each, 256 of four
+        // states send a quarter of them): 111 species, 1024 states 77 -> 82,
+        // 4096 states 208 -> 179.  A wave holds 168 registers, a compute unit 12
+        // waves: taken where the LDS lets in workgroups for all 12, or where a
+        // state needs 8 waves (360 species, 8192 states 1000 -> 650).  53 species,
+        // 65536 states 1047 -> 779 (2 waves; 3: 849), 111 species, 54054 states
+        // 1492 -> 1229 (4 waves; 3: 1744); 160 species, two workgroups:
+        // 1319 -> 1654; 32 species, 208 reactions: 580 -> 651.
+        if (n <= 256) return take(1, blocks <= 8 ? 4 : 8);
+        if (blocks > 4 * GATHER_BLOCKS) return take(1, 8);
+        if (n < 3072 || blocks <= 4) return false;
+        const int v = blocks <= 6 ? 2 : blocks <= 9 ? 3 : 4;
+        return gather_lds(m.gm, GM_ADJ, 1) * (12 / v) <= m.lds_max && take(1, v);
+    }
     if (mode == MODE_SRC) {
         if (n <= 1024) return take(1, 4);
         return n <= 4096 && blocks >= 2 && take(2, blocks <= 6 ? 2 : 4);
@@ -180,9 +195,11 @@ pj_status eval(const pj_mech* mech, int mode, pj_form form, pj_layout layout, in
         return fail(PJ_E_UNSUPPORTED, "per-state working set (" + std::to_string(lds) +
                                           " B) exceeds the LDS of one workgroup");
     int gS = m.S[mode], gw = m.waves[mode];
-    if (m.automatic[mode] ? pj::gather_choice(m, mode, layout, n, gS, gw) : pj::gather_takes(m, mode, layout, n, gS, gw)) {
+    const bool fused = mode == pj::MODE_ADJ && dstate;   // J^T v with source terms: scatter kernels
+    if (!fused && (m.automatic[mode] ? pj::gather_choice(m, mode, layout, n, gS, gw)
+                                     : pj::gather_takes(m, mode, layout, n, gS, gw))) {
         hipError_t e = pj::launch_gather({&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, gS, gw, n, state, param,
-                                          dstate, jac, arr, (hipStream_t)stream});
+                                          dstate, jac, arr, (hipStream_t)stream, vin, grad});
         if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
         g_err.clear();
         return PJ_OK;
@@ -502,7 +519,7 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
             auto go = [&]() {
                 if (gather)
                     return pj::launch_gather({&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, S, wv, n_states,
-                                              d_state, d_param, dst, jac, nullptr, hs});
+                                              d_state, d_param, dst, jac, nullptr, hs, vin, grad});
                 return pj::launch(m.dm, kmode, form, layout, S, n_states, d_state, d_param, dst, jac, vin, grad,
                                   gr ? 1 : 0, wv, l, hs);
             };

@@ -60,6 +60,7 @@
 #ifndef PJ_WPE_SRC
 #define PJ_WPE_SRC 4
 #define PJ_WPE_JAC 4
+#define PJ_WPE_ADJ 3
 #endif
 
 namespace pj {
@@ -67,7 +68,8 @@ namespace {
 
 // per-state scalars in LDS
 enum { SC_LNT = 0, SC_NSUM, SC_CB, SC_ICB, SC_DP, SC_DDP, SC_TT, SC_TS, SC_ST, SC_SS, SC_TDOT, SC_SDOT, SC_OM, SC_SCW,
-       SC_T, SC_V, SC_P, SC_INVT, SC_INVV, SC_INVRT, SC_CTOT, SC_LNP, SC_N };
+       SC_T, SC_V, SC_P, SC_INVT, SC_INVV, SC_INVRT, SC_CTOT, SC_LNP,
+       SC_KAP, SC_VT, SC_VS, SC_LB, SC_N };
 // fields of a species record in LDS: {exp g, C, exp -g, h}, after the
 // reactions {wdot, 1/C, T column sum, h}
 enum { A_E = 0, A_C = 1, A_I = 2, A_H = 3, A_W = 0, A_IC = 1, A_VT = 2 };
@@ -163,18 +165,45 @@ __device__ inline double dpp(double v) {
     const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xF, 0xF, true);
     return __hiloint2double(hi, lo);
 }
-// lane ^ 16 / lane ^ 32: each swap leaves a value and its partner's in a pair
-__device__ inline double add_x16(double v) {
+// a value and that of lane ^ 16 / lane ^ 32, in the same order in both lanes
+__device__ inline void both_x16(double v, double& a, double& b) {
     const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-    const auto a = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
-    const auto b = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
-    return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+    const auto x = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto y = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    a = __hiloint2double((int)y[0], (int)x[0]);
+    b = __hiloint2double((int)y[1], (int)x[1]);
+}
+__device__ inline void both_x32(double v, double& a, double& b) {
+    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
+    const auto x = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto y = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    a = __hiloint2double((int)y[0], (int)x[0]);
+    b = __hiloint2double((int)y[1], (int)x[1]);
+}
+__device__ inline double add_x16(double v) {
+    double a, b;
+    both_x16(v, a, b);
+    return a + b;
 }
 __device__ inline double add_x32(double v) {
-    const unsigned lo = (unsigned)__double2loint(v), hi = (unsigned)__double2hiint(v);
-    const auto a = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
-    const auto b = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
-    return __hiloint2double((int)b[0], (int)a[0]) + __hiloint2double((int)b[1], (int)a[1]);
+    double a, b;
+    both_x32(v, a, b);
+    return a + b;
+}
+// double-double sum over the wave (data-parallel moves: a shuffle through the
+// LDS would add its latency twelve times to the chain)
+__device__ inline dd wave_total(dd v) {
+    v = dd_add(v, dd{dpp<0xB1>(v.hi), dpp<0xB1>(v.lo)});
+    v = dd_add(v, dd{dpp<0x4E>(v.hi), dpp<0x4E>(v.lo)});
+    v = dd_add(v, dd{dpp<0x141>(v.hi), dpp<0x141>(v.lo)});
+    v = dd_add(v, dd{dpp<0x140>(v.hi), dpp<0x140>(v.lo)});
+    double a, b, c, d;
+    both_x16(v.hi, a, b);
+    both_x16(v.lo, c, d);
+    v = dd_add(dd{a, c}, dd{b, d});
+    both_x32(v.hi, a, b);
+    both_x32(v.lo, c, d);
+    return dd_add(dd{a, c}, dd{b, d});
 }
 // sum over the wave
 __device__ inline double wave_total(double v) {
@@ -205,10 +234,12 @@ template <int FORM, int LAYOUT, int MODE, int NV, bool EXT>
 __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                                              const double* __restrict__ state, const double* __restrict__ param,
                                              double* __restrict__ dstate, double* __restrict__ jac,
-                                             const double* __restrict__ arr, const long qg) {
+                                             const double* __restrict__ arr, const long qg,
+                                             const double* __restrict__ vin = nullptr, double* const GR = nullptr) {
     extern __shared__ double lds[];
     typedef double V __attribute__((ext_vector_type(NV)));
-    constexpr bool JAC = MODE != GM_SRC, dense = MODE == GM_DENSE;
+    constexpr bool JAC = MODE == GM_JAC || MODE == GM_DENSE, dense = MODE == GM_DENSE, ADJ = MODE == GM_ADJ;
+    constexpr bool DER = MODE != GM_SRC;
     constexpr int RB = GATHER_BLOCKS;    // most blocks of reactions of a wave
     constexpr int layout = LAYOUT;
     const int ns = gmp->ns, nr = gmp->nr, N = ns + 1, bath = ns - 1;
@@ -217,17 +248,21 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
 
     double* const pool = lds;
     // source terms: the pool holds q only (and an empty reaction's zero)
-    const int npool = JAC ? gmp->npool : ((nr + 2) & ~1);
+    // (the adjoint: without the elements from b3 on)
+    const int npool = JAC ? gmp->npool : ADJ ? gmp->b3 : ((nr + 2) & ~1);
     double* const A = pool + npool * NV;
     double* const CP = A + 4 * (ns + 1) * NV;
     double* const VS = CP + (ns + 1) * NV;          // V/P column sums; before them dCp/dT
-    double* const TQ = VS + (JAC ? (ns + 1) * NV : 0);
-    double* const SQ = TQ + (JAC ? (ns + 1) * NV : 0);
-    double* const BB = SQ + (JAC ? (ns + 1) * NV : 0);
+    double* const TQ = VS + (DER ? (ns + 1) * NV : 0);
+    double* const SQ = TQ + (DER ? (ns + 1) * NV : 0);
+    double* const Y = TQ;                           // adjoint: what a unit of wdot_k adds to v . f
+    double* const VV = SQ;                          // adjoint: v of the species rows
+    double* const BB = SQ + (DER ? (ns + 1) * NV : 0);
     double* const PW = BB + (JAC ? (gmp->n_dense_rows + 1) * NV : 0);
     double* const SC = PW + 7 * NV;
-    double* const RS = SC + SC_N * NV;              // the waves' sums over reactions (4 each)
-    int* const ints = reinterpret_cast<int*>(RS + (JAC ? 4 * (MAX_THREADS / 64) * NV : 0));   // flags of the waves
+    constexpr int NRS = ADJ ? 7 : JAC ? 4 : 0;      // the waves' sums over reactions
+    double* const RS = SC + SC_N * NV;
+    int* const ints = reinterpret_cast<int*>(RS + NRS * (MAX_THREADS / 64) * NV);   // flags of the waves
     // (dynamic LDS starts at address 0: the kernels have no other)
     typedef __attribute__((address_space(3))) V LV;
     auto vec = [](double* p, int i) -> V& { return *reinterpret_cast<V*>(p + i * NV); };
@@ -243,7 +278,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     auto vclamp = [&](const auto& x) { return vmap(x, [](double y) { return clamp_c(y); }); };
     // the reactions of a Jacobian hold too much in registers for several
     // states: there each wave works for one, state rst
-    constexpr int RN = JAC ? 1 : NV;
+    constexpr int RN = DER ? 1 : NV;
     typedef double RV __attribute__((ext_vector_type(RN)));
     const int rst = RN == NV ? 0 : wave % NV, rwave = RN == NV ? wave : wave / NV, rnw = RN == NV ? nwave : nwave / NV;
     auto rvec = [&](double* p, int i) -> RV& { return *reinterpret_cast<RV*>(p + rst + i * NV); };
@@ -276,25 +311,26 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     if (wave == 0) {
         // n_Ns = P V / (R T) - RN(sum of the others)
         dd acc[NV];
-        double T[NV], Sv[NV], Q[NV];
+        double T[NV], Sv[NV], Q[NV], vT[NV], vS[NV];
 #pragma unroll
         for (int v = 0; v < NV; ++v) {
             const long sc = clamp_state(v);
             T[v] = X(sc, 0);
             Sv[v] = X(sc, 1);
             Q[v] = param[sc];
+            if (ADJ) {
+                vT[v] = layout == PJ_LAYOUT_F ? vin[sc] : vin[sc * (long)N];
+                vS[v] = layout == PJ_LAYOUT_F ? vin[n + sc] : vin[sc * (long)N + 1];
+            }
             acc[v] = dd{0.0, 0.0};
         }
         for (int k = lane; k < ns - 1; k += 64)
 #pragma unroll
             for (int v = 0; v < NV; ++v) acc[v] = dd_add(acc[v], dd{X(clamp_state(v), 2 + k), 0.0});
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1)
-#pragma unroll
-            for (int v = 0; v < NV; ++v)
-                acc[v] = dd_add(acc[v], dd{__shfl_xor(acc[v].hi, o, 64), __shfl_xor(acc[v].lo, o, 64)});
+        for (int v = 0; v < NV; ++v) acc[v] = wave_total(acc[v]);
         // lane v finishes state v
-        double t = T[0], sv = Sv[0], q = Q[0], nsum = acc[0].hi;
+        double t = T[0], sv = Sv[0], q = Q[0], nsum = acc[0].hi, wt = ADJ ? vT[0] : 0.0, ws = ADJ ? vS[0] : 0.0;
 #pragma unroll
         for (int v = 1; v < NV; ++v)
             if (lane == v) {
@@ -302,6 +338,10 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 sv = Sv[v];
                 q = Q[v];
                 nsum = acc[v].hi;
+                if (ADJ) {
+                    wt = vT[v];
+                    ws = vS[v];
+                }
             }
         const double Vv = FORM == PJ_CONP ? sv : q, P = FORM == PJ_CONP ? q : sv;
         const double cb = ((P * Vv) / (RU * t) - nsum) / Vv;
@@ -336,6 +376,13 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 put(BB, 0, 0.0);
                 put(pool, gmp->b3 + 2 * nr, 0.0);
                 put(pool, gmp->b3 + 2 * nr + 1, 0.0);
+            } else if (ADJ) {
+                put(SC, SC_VT, wt);
+                put(SC, SC_VS, ws);
+                put(pool, gmp->zero, 0.0);
+                put(CP, ns, 0.0);
+                put(Y, ns, 0.0);
+                put(VV, ns, 0.0);
             } else {
                 put(pool, nr, 0.0);
             }
@@ -383,7 +430,8 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 A[(A_I * (ns + 1) + k) * NV + v] = 1.0 / e;
                 A[(A_H * (ns + 1) + k) * NV + v] = h;
                 CP[k * NV + v] = FORM == PJ_CONP ? cp : cp - 1.0;
-                if (JAC) VS[k * NV + v] = a1 + T * (a(14) + T * (a(15) + T * a(16)));
+                if (ADJ) VV[k * NV + v] = k < ns - 1 ? layout == PJ_LAYOUT_F ? vin[(2 + k) * (long)n + sc] : vin[sc * (long)N + 2 + k] : 0.0;
+                if (DER) VS[k * NV + v] = a1 + T * (a(14) + T * (a(15) + T * a(16)));
             }
         }
     };
@@ -404,19 +452,40 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         __syncthreads();
     }
 
+    // adjoint: J^T v of the reactions is sum_i lambda_i grad q_i with lambda_i =
+    // v_T dTdot/dq_i + v_S dSdot/dq_i + V sum_k nu_ki v_k = sum_k nu_ki Y_k
+    if constexpr (ADJ) {
+        const GatherPtr gm = fresh(gmp);
+        V d0 = 0.0;
+        for (int k = lane; k < ns; k += 64) d0 += SP(k, A_C) * vec(CP, k);
+        const V Dp = vmap(d0, [](double x) { return wave_total(x); });
+        if (wave == 0 && lane == 0) vec(SC, SC_DP) = Dp;
+        for (int it = tid; it < ns * NV; it += nthr) {
+            const int k = NV == 1 ? it : it / NV, v = NV == 1 ? 0 : it - k * NV;
+            auto C_ = [&](int q) { return SC[q * NV + v]; };
+            const double T = C_(SC_T), Vv = C_(SC_V), P = C_(SC_P), vT = C_(SC_VT), vS = C_(SC_VS);
+            const double a = -(vT + vS * (FORM == PJ_CONP ? Vv : P) * C_(SC_INVT)) / (NV == 1 ? Dp[0] : Dp[v]);
+            const double b = vS * RU * T * (FORM == PJ_CONP ? Vv / P : 1.0);
+            const double h = A[(A_H * (ns + 1) + k) * NV + v];
+            Y[k * NV + v] = Vv * VV[k * NV + v] + (a * T) * (FORM == PJ_CONP ? h : h - 1.0) + b * at(gm->wfac, (uint32_t)k);
+            if (k == 0) SC[SC_KAP * NV + v] = a;
+        }
+        __syncthreads();
+    }
+
     // ---- (2) reactions
     if (wave == nwave - 1) {
         V d0 = 0.0, d1 = 0.0;   // D' = sum C chat/R, dD'/dT = sum C dCp/R/dT
         for (int k = lane; k < ns; k += 64) {
             const V c = SP(k, A_C);
             d0 += c * vec(CP, k);
-            if (JAC) d1 += c * vec(VS, k);
+            if (DER) d1 += c * vec(VS, k);
         }
         d0 = vmap(d0, [](double x) { return wave_total(x); });
-        if (JAC) d1 = vmap(d1, [](double x) { return wave_total(x); });
+        if (DER) d1 = vmap(d1, [](double x) { return wave_total(x); });
         if (lane == 0) {
-            vec(SC, SC_DP) = d0;
-            if (JAC) vec(SC, SC_DDP) = d1;
+            if (!ADJ) vec(SC, SC_DP) = d0;
+            if (DER) vec(SC, SC_DDP) = d1;
         }
     }
     // q and dE of this lane's reactions wait in registers while dq/dT and dq/dS
@@ -431,14 +500,17 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         auto K = [&](int q) { return vec(SC, q); };
         auto U = [&](int q) { return RN == 1 ? vmap(K(q), [](double x) { return uniform(x); }) : K(q); };
         const V T = U(SC_T), lnT = U(SC_LNT), invT = U(SC_INVT), Ctot = U(SC_CTOT);
-        const int b3 = JAC ? gm->b3 : 0, neff_rec = gm->neff;
+        const int b3 = DER ? gm->b3 : 0, neff_rec = gm->neff;
         auto vlow = [](const V& x) {
             bool b = false;
 #pragma unroll
             for (int v = 0; v < RN; ++v) b |= x[v] < LNK_MIN;
             return b;
         };
-        V s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0;   // sum dE dq/dT, dE dq/dS, dOmega dq/dT, dOmega dq/dS
+        // sums over reactions: dE dq/dT, dE dq/dS, dOmega dq/dT, dOmega dq/dS;
+        // adjoint: lambda dq/dT, lambda dq/dS, lambda dq/dC_Ns, then the energy, mole,
+        // heat capacity and (CONP) v weighted rates
+        V s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0, s4 = 0.0, s5 = 0.0, s6 = 0.0;
         for (int r = 0; block_of(r) < nblk; ++r) {
             int p = block_of(r) * 64 + lane;
             const bool act = p < nr;
@@ -475,7 +547,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 }
             }
             // slots: concentration products, ratio kr / kf, dH
-            V Pf = 1.0, Pb = 1.0, kq = 1.0, dH = 0.0, dG = 0.0, Pft = 1.0, Pbt = 1.0;
+            V Pf = 1.0, Pb = 1.0, kq = 1.0, dH = 0.0, dG = 0.0, Pft = 1.0, Pbt = 1.0, lam = 0.0, dcp = 0.0, dvv = 0.0;
             {
                 V xs[NSLOT][3];
 #pragma unroll
@@ -486,19 +558,40 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                         const int k = rr.sp[a];
                         xs[a][0] = SP(k, A_C);
                         xs[a][1] = SP(k, a < MAXSIDE ? A_I : A_E);
-                        if (JAC) xs[a][2] = SP(k, A_H);
+                        if (DER) xs[a][2] = SP(k, A_H);
                     }
                 }
                 PJ_READS_FIRST();
                 Pf = xs[0][0] * xs[1][0] * xs[2][0];
                 Pb = xs[3][0] * xs[4][0] * xs[5][0];
                 kq = (xs[0][1] * xs[3][1]) * (xs[1][1] * xs[4][1]) * (xs[2][1] * xs[5][1]);
-                if (JAC) dH = ((xs[3][2] - xs[0][2]) + (xs[4][2] - xs[1][2])) + (xs[5][2] - xs[2][2]);
-                if (JAC && tiny) {
+                if (DER) dH = ((xs[3][2] - xs[0][2]) + (xs[4][2] - xs[1][2])) + (xs[5][2] - xs[2][2]);
+                if (DER && tiny) {
                     // absent species at 1e-150
                     Pft = vclamp(xs[0][0]) * vclamp(xs[1][0]) * vclamp(xs[2][0]);
                     Pbt = vclamp(xs[3][0]) * vclamp(xs[4][0]) * vclamp(xs[5][0]);
                 }
+            }
+            if constexpr (ADJ) {
+                // read after the products are formed: the registers of both
+                // sets at once would spill
+                PJ_READS_FIRST();
+                V xa[NSLOT][3];
+#pragma unroll
+                for (int a = 0; a < NSLOT; ++a) {
+                    xa[a][0] = xa[a][1] = xa[a][2] = 0.0;
+                    if ((cm >> a) & 1) {
+                        const int k = rr.sp[a];
+                        xa[a][0] = vec(Y, k);
+                        xa[a][1] = vec(CP, k);
+                        if (FORM == PJ_CONP) xa[a][2] = vec(VV, k);
+                    }
+                }
+                PJ_READS_FIRST();
+                auto delta = [&](int f) { return ((xa[3][f] - xa[0][f]) + (xa[4][f] - xa[1][f])) + (xa[5][f] - xa[2][f]); };
+                lam = delta(0);
+                dcp = delta(1);
+                if (FORM == PJ_CONP) dvv = delta(2);
             }
             if (logs)
 #pragma unroll
@@ -528,7 +621,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                     }
             }
             // pressure modification
-            V c = 1.0, dcdM = 0.0, dcdT = 0.0;
+            V c = 1.0, dcdM = 0.0, dcdT = 0.0, Pr_dcdPr = 0.0, qA = 1.0;
             if (!PLAIN && kind == K_THREEBODY) {
                 c = Ctot + Meff;
                 dcdM = 1.0;
@@ -562,7 +655,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                     const V den = 1.0 + f * f;
                     const V lF = lf / den;
                     F = vexp(LN10 * lF);
-                    if (JAC) {
+                    if (DER) {
                         const V gg = -2.0 * lf * f / (den * den);
                         dlF_dlP = gg * nn / (Bd * Bd);
                         const V df_dL = (-0.67 * Bd + 1.1762 * Aa) / (Bd * Bd);
@@ -579,7 +672,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                     const V lb = vlog10(base);
                     const V lF = fr_.p[3] + Xs * lb + ee * lnT * (1.0 / LN10);
                     F = vexp(LN10 * lF);
-                    if (JAC) {
+                    if (DER) {
                         dlF_dlP = -2.0 * lb * lP * Xs * Xs;
                         const V dbase = a * bb * invT * invT * eb - ic * ec;
                         dlF_dT = (Xs * dbase / base + ee * invT) * (1.0 / LN10);
@@ -588,20 +681,22 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 const V ip = 1.0 / (1.0 + Pr);
                 const bool chemact = EXT && (cm & CHUNK_CHEMACT) && (w & GI_CHEMACT);
                 c = chemact ? F * rk * ip : F * Pr * ip;
-                if (JAC) {
+                if (DER) {
                     const V dlnPr = (fr_.b0 + fr_.theta0 * invT) * invT - (bexp + th * invT) * invT;
                     if (!chemact) {
                         const V dc_dPr = F * ip * ip + F * ip * dlF_dlP;
                         dcdM = dc_dPr * rk;
+                        if (ADJ) Pr_dcdPr = Pr * dc_dPr;
                         dcdT = dc_dPr * Pr * dlnPr + c * LN10 * dlF_dT;
                     } else {
                         dcdM = c * (dlF_dlP / M - rk * ip);
                         dcdT = c * (ip + dlF_dlP) * dlnPr + c * LN10 * dlF_dT;
+                        if (ADJ) qA = Pr * ip - dlF_dlP;
                     }
                 }
             }
             const V q = PLAIN ? R : c * R;
-            if constexpr (!JAC) {
+            if constexpr (!DER) {
                 if (act) PO(p) = q;
             } else {
                 const V invV = K(SC_INVV);
@@ -633,23 +728,43 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 const V dqdS = FORM == PJ_CONP ? -(sQC - Qb * (K(SC_NSUM) * invV)) * invV
                                                : Qc * K(SC_INVRT) + q * dlkt_dP;
                 const V dE = FORM == PJ_CONP ? dH : dH - dnu;
+                if constexpr (JAC) {
 #pragma unroll
-                for (int k = 0; k < RB; ++k)
-                    if (r == k) {
-                        hq[k] = q;
-                        he[k] = dE;
+                    for (int k = 0; k < RB; ++k)
+                        if (r == k) {
+                            hq[k] = q;
+                            he[k] = dE;
+                        }
+                    if (act) {
+                        PO(p) = Fw;
+                        if (rev) PO(rr.bpos) = Bk;
+                        PO(b3 + 2 * p) = dqdT;
+                        PO(b3 + 2 * p + 1) = dqdS;
+                        if ((w & GI_BATH) && !gm->approx) PO(rr.qbpos) = Qb;
+                        s0 += dE * dqdT;
+                        s1 += dE * dqdS;
+                        s2 += rr.domega * dqdT;
+                        s3 += rr.domega * dqdS;
                     }
-                if (act) {
-                    PO(p) = Fw;
-                    if (rev) PO(rr.bpos) = Bk;
-                    PO(b3 + 2 * p) = dqdT;
-                    PO(b3 + 2 * p + 1) = dqdS;
-                    if ((w & GI_BATH) && !gm->approx) PO(rr.qbpos) = Qb;
-                    s0 += dE * dqdT;
-                    s1 += dE * dqdS;
-                    s2 += rr.domega * dqdT;
-                    s3 += rr.domega * dqdS;
+                } else if (act) {
+                    PO(p) = lam * Fw;
+                    if (rev) PO(rr.bpos) = lam * Bk;
+                    s0 += lam * dqdT;
+                    s1 += lam * dqdS;
+                    if (w & GI_BATH) s2 += lam * Qb;
+                    s3 += q * dE;
+                    s4 += rr.domega * q;
+                    s5 += q * dcp;
+                    if (FORM == PJ_CONP) s6 += q * dvv;
+                    if (GR) {
+                        // (this lane's own element: added to without atomics)
+                        const double g = (PLAIN ? lam * q : lam * (q * qA - R * Pr_dcdPr))[0];
+                        GR[p] += g;
+                        GR[nr + p] += g * lnT[0];
+                        GR[2 * nr + p] -= g * invT[0];
+                    }
                 }
+                const V QMl = ADJ ? lam * QM : QM;
                 if (!PLAIN && neffc) {
                     // third-body terms Q_M (alpha_k - 1) C_k, the record read again (cache hit)
                     const int neff = act ? (int)((w >> 24) & 0xF) : 0;
@@ -660,9 +775,9 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                         if (2 * h < neffc) {
                             const uint4 u = at4(eq, ei + 1 + h);
                             if (2 * h < neff)
-                                PO(rr.tpos + 2 * h) = QM * __hiloint2double(u.y, u.x) * vclamp(SP(es[h] & 0xFFFF, A_C));
+                                PO(rr.tpos + 2 * h) = QMl * __hiloint2double(u.y, u.x) * vclamp(SP(es[h] & 0xFFFF, A_C));
                             if (2 * h + 1 < neff)
-                                PO(rr.tpos + 2 * h + 1) = QM * __hiloint2double(u.w, u.z) * vclamp(SP(es[h] >> 16, A_C));
+                                PO(rr.tpos + 2 * h + 1) = QMl * __hiloint2double(u.w, u.z) * vclamp(SP(es[h] >> 16, A_C));
                         }
                 }
             }
@@ -671,17 +786,12 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             else react(std::false_type());
             if (block_of(r + 1) < nblk) nxt = rec_at(gm, block_of(r + 1));
         }
-        if (JAC) {
-            auto all = [&](const V& x) { return vmap(x, [](double y) { return wave_total(y); }); };
-            s0 = all(s0);
-            s1 = all(s1);
-            s2 = all(s2);
-            s3 = all(s3);
-            if (lane == 0) {
-                vec(RS, 4 * rwave) = s0;
-                vec(RS, 4 * rwave + 1) = s1;
-                vec(RS, 4 * rwave + 2) = s2;
-                vec(RS, 4 * rwave + 3) = s3;
+        if constexpr (DER) {
+            V sums[7] = {s0, s1, s2, s3, s4, s5, s6};
+#pragma unroll
+            for (int c = 0; c < NRS; ++c) {
+                sums[c] = vmap(sums[c], [](double y) { return wave_total(y); });
+                if (lane == 0) vec(RS, NRS * rwave + c) = sums[c];
             }
         }
     }
@@ -739,6 +849,81 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             words(y.z, y.w);
         }
     };
+    if constexpr (ADJ) {
+        // columns: sum over the reactions that depend on species j, over [C]_j
+        const GatherPtr gm = fresh(gmp);
+        const int ntask = gm->cl.n;
+        auto load = [&](int t) { return t < ntask ? list_at(gm->cl, t) : no_task(); };
+        Task nx = load(wave);
+        __syncthreads();
+        if (wave == nwave - 1) {
+            V t[NRS];
+#pragma unroll
+            for (int c = 0; c < NRS; ++c) {
+                t[c] = 0.0;
+                for (int w = 0; w < rnw; ++w) t[c] += vec(RS, NRS * w + c);
+            }
+            const V T = K(SC_T), Vv = K(SC_V), P = K(SC_P), iT = K(SC_INVT), iV = K(SC_INVV), ct = K(SC_CTOT), Dp = K(SC_DP);
+            const V kap = K(SC_KAP), vS = K(SC_VS), cpb = vec(CP, bath);
+            const V Tdot = -T * t[3] / Dp, Om = t[4];
+            const V dDdT = K(SC_DDP) - cpb * ct * iT;
+            const V dDdS = FORM == PJ_CONP ? -((Dp - cpb * K(SC_CB)) - cpb * (K(SC_NSUM) * iV)) * iV : cpb / (RU * T);
+            const V X = FORM == PJ_CONP ? Vv : P;
+            const V jT = t[0] + kap * (t[5] + Tdot * dDdT) +
+                         vS * ((FORM == PJ_CONP ? Vv * (RU / P) * Om : RU * Om) - X * Tdot * iT * iT);
+            V jS = t[1] + kap * Tdot * dDdS + vS * Tdot * iT;
+            if (FORM == PJ_CONP) jS += vS * (RU * T / P) * Om + t[6];
+            if (lane == 0) {
+                vec(SC, SC_TT) = jT;
+                vec(SC, SC_TS) = jS;
+                vec(SC, SC_LB) = gm->approx ? V(0.0) : t[2];
+                vec(SC, SC_KAP) = kap * Tdot * iV;
+                vec(SC, SC_CB) = gm->approx ? V(0.0) : cpb;
+            }
+        }
+        for (int t = wave; t < ntask; t += nwave) {
+            const Task k = nx;
+            nx = load(t + nwave);
+            int most, nm, lp, what;
+            bool first;
+            task_of(k, most, nm, first, lp, what);
+            V w0 = 0.0;
+            auto words = [&](const uint32_t* x, auto nw) {
+                constexpr int NW = decltype(nw)::value;
+                V v[NW];
+#pragma unroll
+                for (int c = 0; c < NW; ++c) v[c] = PO((int)((x[c] & 0xFFF8) >> 3));
+                PJ_READS_FIRST();
+#pragma unroll
+                for (int c = 0; c < NW; ++c) w0 += sign0(x[c]) * v[c];
+            };
+            const uint32_t hw[7] = {k.h.y, k.h.z, k.h.w, k.x.x, k.x.y, k.x.z, k.x.w};
+            words(hw, std::integral_constant<int, 7>());
+            for (int c = 0; c < nm; ++c) {
+                const uint4 y = at4(gm->cl.more, (k.d.y + c) * 64 + lane);
+                const uint32_t x[4] = {y.x, y.y, y.z, y.w};
+                words(x, std::integral_constant<int, 4>());
+            }
+            w0 = vmap(w0, [&](double y) { return fold(y, most, lp); });
+            if (first) SP(what, A_E) = w0 / vclamp(SP(what, A_C));
+        }
+        __syncthreads();
+        const int G = nthr / NV;
+        const int s2 = NV == 1 ? 0 : layout == PJ_LAYOUT_F ? tid % NV : tid / G;
+        const int g2 = NV == 1 ? tid : layout == PJ_LAYOUT_F ? tid / NV : tid - s2 * G;
+        const long st2 = qg * NV + s2;
+        if (st2 < n) {
+            auto C_ = [&](int q) { return SC[q * NV + s2]; };
+            const double lb = C_(SC_LB), kt = C_(SC_KAP), cpb = C_(SC_CB), iV = C_(SC_INVV);
+            for (int i = g2; i < N; i += G) {
+                const int k = (i - 2) * NV + s2;
+                const double y = i == 0 ? C_(SC_TT) : i == 1 ? C_(SC_TS) : iV * (A[k] - lb) + kt * (CP[k] - cpb);
+                if (layout == PJ_LAYOUT_F) jac[(long)i * n + st2] = y;
+                else jac[st2 * (long)N + i] = y;
+            }
+        }
+        return;
+    }
     if constexpr (JAC) {
         // (3a) T and V/P columns of the species rows; bath-gas partials
         const GatherPtr gm = fresh(gmp);
@@ -890,7 +1075,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
                     V t = 0.0;
-                    for (int w = 0; w < rnw; ++w) t += vec(RS, 4 * w + c);
+                    for (int w = 0; w < rnw; ++w) t += vec(RS, NRS * w + c);
                     vec(SC, SC_TT + c) = t;
                 }
             }
@@ -1151,6 +1336,68 @@ pj_gather_kernel(const GatherMech* const gmp, const long n, const long ngroups, 
     gather_group<FORM, LAYOUT, MODE, NV, EXT>((GatherPtr)gmp, n, state, param, dstate, jac, arr, qg);
 }
 
+// J^T v and the parameter sums, a state per workgroup.  With dE_i, dOmega_i and
+// v known before the reactions, all that v^T J takes of reaction i is lambda_i
+// grad q_i: the pool holds lambda_i F_i, lambda_i B_i and lambda_i T_ik, and a
+// species column is one gathered sum, where the scatter kernels add every
+// partial to three accumulators.  Persistent workgroups, which sum their
+// states' parameter derivatives in LDS (each element has one lane) and add them
+// to the output once.  111 species, 784 reactions, 65536 states: 1.47 ms
+// against 1.80 (scatter, 4 states and 4 waves); 7,600 vector instructions a
+// state, 62% of the issue slots at 12 waves a compute unit.  At 128 registers
+// (16 waves) 66 spilled ones made it 2.46 ms.
+template <int FORM, int LAYOUT, bool EXT>
+__global__ void __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(PJ_WPE_ADJ)))
+pj_gather_adjoint(const GatherMech* const gmp, const long n, const int gr_offset,
+                  const double* __restrict__ state, const double* __restrict__ param, const double* __restrict__ vin,
+                  double* __restrict__ jtv, double* __restrict__ grad, const double* __restrict__ arr) {
+    extern __shared__ double lds[];
+    double* const GR = grad ? lds + gr_offset : nullptr;
+    const int nr = gmp->nr;
+    if (grad)
+        for (int i = threadIdx.x; i < 3 * nr; i += blockDim.x) GR[i] = 0.0;
+    __syncthreads();
+    long q0, q1, qstep;
+    group_range(n, q0, q1, qstep);
+    for (long q = q0; q < q1; q += qstep) {
+        gather_group<FORM, LAYOUT, GM_ADJ, 1, EXT>(fresh((GatherPtr)gmp), n, state, param, nullptr, jtv, arr, q, vin, GR);
+        __syncthreads();
+    }
+    // (each workgroup from a place of its own, so that they don't meet at one
+    // address)
+    if (grad)
+        for (int i = threadIdx.x; i < nr; i += blockDim.x) {
+            int p = i + (int)(blockIdx.x * 61 % (unsigned)nr);
+            if (p >= nr) p -= nr;
+            const int o = gmp->orig[p];
+            atomicAdd(&grad[o], GR[p]);
+            atomicAdd(&grad[nr + o], GR[nr + p]);
+            atomicAdd(&grad[2 * nr + o], GR[2 * nr + p]);
+        }
+}
+
+template <int FORM, int LAYOUT, bool EXT>
+static hipError_t launch_gather_adjoint_t(const GatherCall& c) {
+    auto k = pj_gather_adjoint<FORM, LAYOUT, EXT>;
+    const int64_t lds = gather_lds(*c.gm, GM_ADJ, 1), sums = 24 * (int64_t)c.gm->nr;
+    if (lds > 65536) {
+        static std::atomic<uint64_t> done{0};
+        hipError_t e = allow_full_lds((const void*)k, done);
+        if (e != hipSuccess) return e;
+    }
+    // as many workgroups as the chip holds at 4 * PJ_WPE_ADJ waves a compute unit
+    const int64_t cap = 256 * std::max<int64_t>(1, 4 * PJ_WPE_ADJ / c.waves);
+    int64_t grid = c.n < cap ? c.n : cap;
+    if (grid >= 8) grid &= ~(int64_t)7;
+    if (c.grad) {
+        hipError_t e = zero_async(c.grad, 3 * (int64_t)c.gm->nr, c.stream);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k, dim3((unsigned)grid), dim3(64 * c.waves), (size_t)lds, c.stream, c.d_gm, (long)c.n,
+                       (int)((lds - sums) / 8), c.state, c.param, c.vin, c.jac, c.grad, c.arr);
+    return hipGetLastError();
+}
+
 template <int FORM, int LAYOUT, int MODE, int NV, bool EXT>
 static hipError_t launch_gather_t(const GatherCall& c) {
     auto k = pj_gather_kernel<FORM, LAYOUT, MODE, NV, EXT>;
@@ -1172,17 +1419,21 @@ template <bool EXT>
 hipError_t launch_gather_impl(const GatherCall& c) {
 #define PJ_G(F, L, M, SS) \
     if (c.form == F && c.layout == L && c.gmode == M && c.S == SS) return launch_gather_t<F, L, M, SS, EXT>(c);
+#define PJ_GA(F, L) \
+    if (c.form == F && c.layout == L && c.gmode == GM_ADJ && c.S == 1) return launch_gather_adjoint_t<F, L, EXT>(c);
 #ifdef PJ_QUICK
+    PJ_GA(PJ_CONP, PJ_LAYOUT_C)
 #define PJ_GS(F, L, M) PJ_G(F, L, M, 1) PJ_G(F, L, M, 2)
     PJ_GS(PJ_CONP, PJ_LAYOUT_C, GM_SRC) PJ_GS(PJ_CONP, PJ_LAYOUT_C, GM_JAC)
 #else
 #define PJ_GS(F, L, M) PJ_G(F, L, M, 1) PJ_G(F, L, M, 2)
-#define PJ_GL(F, L) PJ_GS(F, L, GM_SRC) PJ_GS(F, L, GM_JAC) PJ_GS(F, L, GM_DENSE)
+#define PJ_GL(F, L) PJ_GS(F, L, GM_SRC) PJ_GS(F, L, GM_JAC) PJ_GS(F, L, GM_DENSE) PJ_GA(F, L)
     PJ_GL(PJ_CONP, PJ_LAYOUT_C) PJ_GL(PJ_CONP, PJ_LAYOUT_F) PJ_GL(PJ_CONV, PJ_LAYOUT_C) PJ_GL(PJ_CONV, PJ_LAYOUT_F)
 #undef PJ_GL
 #endif
 #undef PJ_GS
 #undef PJ_G
+#undef PJ_GA
     return hipErrorInvalidValue;
 }
 

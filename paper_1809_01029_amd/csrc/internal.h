@@ -245,7 +245,7 @@ struct GatherMech {
     const PJ_GLOBAL JacRound* rounds;
 };
 constexpr int GATHER_BLOCKS = 5;     // most 64-reaction blocks of a wave
-enum GatherMode : int { GM_SRC = 0, GM_JAC = 1, GM_DENSE = 2 };
+enum GatherMode : int { GM_SRC = 0, GM_JAC = 1, GM_DENSE = 2, GM_ADJ = 3 };
 
 struct Mechanism {
     // host copy of the description
@@ -359,6 +359,8 @@ struct GatherCall {
     double *dstate, *jac;
     const double* arr;               // as DevMech::arr
     hipStream_t stream;
+    const double* vin;               // adjoint: v, and the parameter sums (or null)
+    double* grad;
 };
 hipError_t launch_gather(const GatherCall& c);
 hipError_t launch_gather_ext(const GatherCall& c);

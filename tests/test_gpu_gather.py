@@ -128,3 +128,42 @@ def test_arrhenius_of_the_mechanism_and_the_call(torch_cuda, api, mech_dir):
     for g in got[:2]:
         for a, c in zip(g, got[2]):
             assert bool(((a - c).abs() <= 1e-12 * c.abs().amax(dim=1, keepdim=True)).all())
+
+
+@pytest.mark.parametrize("shape", [(1, 2), (1, 3), (1, 4), (1, 8)])
+@pytest.mark.parametrize("form,layout", [("conp", "C"), ("conv", "F")])
+@pytest.mark.parametrize("case", [("tiny", 1, ""), ("tiny", 5, "absent"), ("ns13", 3, ""), ("ns53", 9, ""),
+                                  ("ns53", 7, "absent"), ("ns111", 5, ""), ("ns111x", 3, "")])
+def test_gather_adjoint(torch_cuda, api, case, form, layout, shape, mech_dir):
+    """J^T v and the parameter sums, with the mechanism's and the call's
+    Arrhenius parameters, exact and approximate, with and without the sums.
+    The gates of the Jacobian; where species are absent or a column is a small
+    difference of large sums, the oracle's running error bound widens them."""
+    torch = torch_cuda
+    name, n, edge = case
+    m, path = tiny_file(3, mech_dir, bath_reactions=1, bath_efficiency=True) if name == "tiny" else workload_file(name, mech_dir)
+    x, p = states(m, n, form, 7, edge)
+    v = np.random.default_rng(3).standard_normal(x.shape)
+    o = oracle.Oracle(path)
+    print("case", name, n, edge, form, layout, shape, flush=True)
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a if layout == "C" else a.T)).cuda()  # noqa: E731
+    host = lambda a: a.cpu().numpy() if layout == "C" else a.cpu().numpy().T  # noqa: E731
+    xs, vs, ps = dev(x), dev(v), torch.from_numpy(p.copy()).cuda()
+    j_o, g_o, j_s, g_s = o.adjoint(x, p, v, form, bound=True)
+    mech = api.load_mechanism(path)
+    mech.set_launch(*shape)
+    for arr in (None, torch.as_tensor(np.stack(mech.arrhenius())).cuda()):
+        j, g = api.eval_adjoint(mech, xs, ps, vs, form, layout, arrhenius=arr)
+        check_jac(host(j), j_o, j_s, "J^T v")
+        check_jac(g.cpu().numpy(), g_o, g_s, "parameter derivatives")
+    j2, g2 = api.eval_adjoint(mech, xs, ps, vs, form, layout, with_grad=False)
+    assert g2 is None and torch.equal(j, j2)
+    # the approximate Jacobian's product
+    mech = api.load_mechanism(path, api.OPT_APPROX_JACOBIAN)
+    mech.set_launch(*shape)
+    j, _ = api.eval_adjoint(mech, xs, ps, vs, form, layout)
+    J, S = o.jacobian(x, p, form, bound=True, approx=True)
+    jo = np.einsum("sij,si->sj", J, v)
+    # bound: every entry's own, and the rounding of the sum of N products
+    so = np.einsum("sij,si->sj", S, np.abs(v)) + J.shape[1] * 2.3e-16 * np.einsum("sij,si->sj", np.abs(J), np.abs(v))
+    check_jac(host(j), jo, so, "approximate J^T v")
