@@ -243,6 +243,7 @@ pj_status pj_mech_get_arrhenius(const pj_mech* mech, double* lnA, double* b, dou
  * mapping (a lane per state).  0 restores the automatic choice, which
  * depends on the call's states and layout: few states and, for Jacobians,
  * mechanisms of more than 256 reactions take one or two states per workgroup;
+ * source terms of many states take 64, or two of large mechanisms;
  * the others the most states, up to 4, whose working set fits the LDS of one
  * workgroup, and enough waves for about 8 resident waves per compute unit.  A
  * states_per_group that does not fit for a mode is ignored for that mode.
@@ -252,6 +253,9 @@ pj_status pj_mech_get_arrhenius(const pj_mech* mech, double* lnA, double* b, dou
  * run-time slot search or the fixed-order additions.  So does the adjoint with
  * one state (without fused source terms); its parameter sums are added over
  * the workgroups in any order.
+ * Source terms of 64 states with at least 2 waves run a lane per state where
+ * four rows of the species fit the LDS (about 75 species); there
+ * waves_per_group counts pairs of waves.
  * With one wave per workgroup every accumulation happens in a fixed order
  * too, so results are bitwise reproducible; with more (and 4 or more states),
  * the order of LDS atomic additions across waves may vary between runs

@@ -20,7 +20,7 @@ HIPCC = os.environ.get("HIPCC", shutil.which("hipcc") or "/opt/rocm/bin/hipcc")
 COMMON = ["-O3", "-fPIC", "-std=c++17", "-I", INCLUDE, "-I", CSRC, "-Wall"]
 # packed FP32 instructions stay disabled in every device compile
 DEVICE = [f"--offload-arch={ARCH}", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
-# the gather kernels run each loop a few times per state: constants hoisted out
+# the gather and wide kernels run each loop a few times per state: constants hoisted out
 # of them (the coefficients of exp and log10) only hold registers
 GATHER = ["-mllvm", "-disable-machine-licm"]
 
@@ -38,11 +38,11 @@ def build(verbose: bool = False) -> str:
     os.makedirs(BUILD, exist_ok=True)
     jobs = []
     for src in ("mech.cpp", "api.cpp", "batch.cpp", "kernels.hip", "kernels_conv.hip", "kernels_ext.hip",
-                "kernels_ext_conv.hip", "gather.cpp", "gather.hip", "gather_ext.hip", "calibrate.hip", "noalloc.hip"):
+                "kernels_ext_conv.hip", "gather.cpp", "gather.hip", "gather_ext.hip", "wide.hip", "wide_ext.hip", "calibrate.hip", "noalloc.hip"):
         o = os.path.join(BUILD, src + ".o")
         # host-only translation units: no device pass
         dev = DEVICE if src.endswith(".hip") else ["--offload-host-only"]
-        if src.startswith("gather"):
+        if src.startswith(("gather", "wide")):
             dev = dev + GATHER
         jobs.append(([HIPCC] + COMMON + dev + ["-c", os.path.join(CSRC, src), "-o", o], o))
     # the translation units compile in parallel (the two kernel sets dominate)

@@ -66,6 +66,34 @@ static bool gather_takes(const Mechanism& m, int mode, pj_layout layout, int64_t
     return gather_lds(m.gm, gather_mode(mode), S) <= m.lds_max;
 }
 
+// Source terms of 64 states per workgroup and at least 2 waves (pairs of them)
+// run on the wide kernel (wide_body.h).
+static bool wide_takes(const Mechanism& m, int mode, int S, int w) {
+    return mode == MODE_SRC && m.gm.ok && !m.dm.det && S == 64 && w >= 2 && wide_lds(m.gm, w) <= m.lds_max;
+}
+
+// The automatic choice of the wide kernel.  Measured on MI355X, scatter (4
+// states and one wave a workgroup) -> wide, us per call: 13 species, 16384
+// states 19 -> 12, 262144 states 214 -> 77; 20 species 497 -> 214; 53 species,
+// 16384 states 76 -> 43, 262144 states 922 -> 599; 8192 states, half the chip's
+// compute units: 42 -> 40, 13 species 11 -> 11.
+static bool wide_choice(const Mechanism& m, int mode, int64_t n, int& S, int& w) {
+    if (mode != MODE_SRC || n <= 8192) return false;
+    // the waves that fill a compute unit best, the fewest of equals; while the
+    // chip isn't full, many
+    int best = 0;
+    for (int v = 2; v <= 8; v *= 2) {
+        if (!wide_takes(m, mode, 64, v)) continue;
+        const int waves = n <= 16384 ? (v == (m.nr > 64 ? 8 : 4) ? 2 : 1)
+                                     : (int)std::min<int64_t>(16, m.lds_max / wide_lds(m.gm, v) * (2 * v));
+        if (waves <= best) continue;
+        best = waves;
+        S = 64;
+        w = v;
+    }
+    return best > 0;
+}
+
 // The automatic choice between the gather and the scatter kernels for a call
 // of n states, and the gather kernels' shape (false: scatter, in the shape of
 // choose_launch).  Measured on MI355X, scatter -> gather, us per call:
@@ -104,8 +132,12 @@ static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_
         return gather_lds(m.gm, GM_ADJ, 1) * (12 / v) <= m.lds_max && take(1, v);
     }
     if (mode == MODE_SRC) {
+        // the wide kernel's LDS holds about 75 species; of more, scatter -> gather:
+        // 80 species, 262144 states 1410 -> 1220, 111 species 2430 -> 1723, 360
+        // species, 65536 states 5413 -> 1563
         if (n <= 1024) return take(1, 4);
-        return n <= 4096 && blocks >= 2 && take(2, blocks <= 6 ? 2 : 4);
+        if (!(n <= 4096 && blocks >= 2) && !(n <= 8192 && blocks >= 5) && wide_takes(m, mode, 64, 8)) return false;
+        return blocks >= 2 && take(2, blocks <= 9 ? 2 : 4);
     }
     if (!few && blocks <= 4) return false;
     // layout F: two states write twice as long runs; one if two leave a compute
@@ -127,6 +159,8 @@ static void nominal_shape(const Mechanism& m, int mode, int& S, int& w, int64_t&
     const int64_t n = 1 << 20;
     if (m.automatic[mode] ? gather_choice(m, mode, PJ_LAYOUT_C, n, S, w) : gather_takes(m, mode, PJ_LAYOUT_C, n, S, w))
         lds = gather_lds(m.gm, gather_mode(mode), S);
+    else if (m.automatic[mode] ? wide_choice(m, mode, n, S, w) : wide_takes(m, mode, S, w))
+        lds = wide_lds(m.gm, w);
 }
 
 // Waves per workgroup for S states per workgroup: enough that a compute unit
@@ -158,6 +192,13 @@ void choose_launch(Mechanism& m) {
         const int maxS = max_states(kernel_mode(m, mode, false));
         if (m.user_S && m.user_S <= maxS && L(m.user_S, m.user_waves ? m.user_waves : 1) <= m.lds_max)
             S = m.user_S;
+        if (wide_takes(m, mode, m.user_S, m.user_waves)) {
+            m.automatic[mode] = false;
+            m.S[mode] = m.user_S;
+            m.waves[mode] = m.user_waves;
+            m.lds[mode] = wide_lds(m.gm, m.user_waves);
+            continue;
+        }
         int w = m.user_waves ? m.user_waves : default_waves(m, mode, S, gr);
         if (L(S, w) > m.lds_max) w = default_waves(m, mode, S, gr);
         m.S[mode] = S;
@@ -200,6 +241,13 @@ pj_status eval(const pj_mech* mech, int mode, pj_form form, pj_layout layout, in
                                      : pj::gather_takes(m, mode, layout, n, gS, gw))) {
         hipError_t e = pj::launch_gather({&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, gS, gw, n, state, param,
                                           dstate, jac, arr, (hipStream_t)stream, vin, grad});
+        if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
+        g_err.clear();
+        return PJ_OK;
+    }
+    if (m.automatic[mode] ? pj::wide_choice(m, mode, n, gS, gw) : pj::wide_takes(m, mode, gS, gw)) {
+        hipError_t e = pj::launch_wide({&m.gm, m.d_gm, m.dm.ext, pj::GM_SRC, form, layout, gS, gw, n, state, param, dstate,
+                                        nullptr, arr, (hipStream_t)stream, nullptr, nullptr});
         if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
         g_err.clear();
         return PJ_OK;
@@ -515,8 +563,12 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
             const int64_t l = pj::lds_bytes(m.dm, mode, S, wv, gr);
             // a shape that the gather kernels take is theirs (timed once)
             const bool gather = pj::gather_takes(m, mode, layout, n_states, S, wv);
-            if (l > m.lds_max || (gather && du != 16)) continue;
+            const bool wide = pj::wide_takes(m, mode, S, wv);
+            if ((!wide && l > m.lds_max) || (gather && du != 16)) continue;
             auto go = [&]() {
+                if (wide)
+                    return pj::launch_wide({&m.gm, m.d_gm, m.dm.ext, pj::GM_SRC, form, layout, S, wv, n_states, d_state,
+                                            d_param, dst, nullptr, nullptr, hs, nullptr, nullptr});
                 if (gather)
                     return pj::launch_gather({&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, S, wv, n_states,
                                               d_state, d_param, dst, jac, nullptr, hs, vin, grad});
@@ -549,7 +601,8 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
     m.automatic[mode] = false;
     m.S[mode] = best_S;
     m.waves[mode] = best_w;
-    m.lds[mode] = pj::lds_bytes(m.dm, mode, best_S, best_w, gr);
+    m.lds[mode] = pj::wide_takes(m, mode, best_S, best_w) ? pj::wide_lds(m.gm, best_w)
+                                                          : pj::lds_bytes(m.dm, mode, best_S, best_w, gr);
     if (mode == pj::MODE_DENSE) m.dense_unroll = best_du;
     if (states_per_group) *states_per_group = best_S;
     if (waves_per_group) *waves_per_group = best_w;

@@ -186,6 +186,7 @@ void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std:
         R.theta = old.theta;
         R.domega = old.domega;
         R.info = w;
+        R.orig = (uint32_t)g.order[p];
     }
     // dOmega = sum nu (1 - W/W_Ns) is the change of moles, sum nu, when the
     // weights balance as the elements do (each term then carries only its
@@ -234,6 +235,7 @@ void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std:
             }
     if (el >= 8190) return;
     gm.neff = (int)g.eff.size() - 1;
+    gm.nfall = (int)g.fall.size();
     gm.zero = el++;
     el += el & 1;
     gm.b3 = el;

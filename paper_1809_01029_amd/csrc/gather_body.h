@@ -134,7 +134,8 @@ __device__ inline double sconst(double c) {
 // exp(x): x = n ln 2 + r, |r| <= ln(2)/2, in two steps (Cody and Waite), then
 // 1 + r + r^2 q(r) with q of degree 9 interpolating (exp(r) - 1 - r)/r^2 at the
 // Chebyshev nodes (error 1.3e-17), and the scale by 2^n.
-__device__ inline double fexp(double x) {
+// fexp_in: |x| < 708.
+__device__ inline double fexp_in(double x) {
     const double n = __builtin_rint(x * sconst(0x1.71547652b82fep+0));
     double r = fma(-n, sconst(0x1.62e42fefa39efp-1), x);
     r = fma(-n, sconst(0x1.abc9e3b39803fp-56), r);
@@ -148,9 +149,88 @@ __device__ inline double fexp(double x) {
     q = fma(q, r, sconst(0x1.5555555553d63p-5));
     q = fma(q, r, sconst(0x1.5555555555556p-3));
     q = fma(q, r, 0.5);
-    double y = ldexp(1.0 + fma(r * r, q, r), (int)n);
+    return ldexp(1.0 + fma(r * r, q, r), (int)n);
+}
+__device__ inline double fexp(double x) {
+    double y = fexp_in(x);
     y = x > 710.0 ? __builtin_inf() : y;
     return x < -746.0 ? 0.0 : y;
+}
+
+// f on every element
+template <class V, class F>
+__device__ inline V vmap(V x, F f) {
+#pragma unroll
+    for (int v = 0; v < (int)(sizeof(x) / 8); ++v) x[v] = f(x[v]);
+    return x;
+}
+template <class V>
+__device__ inline V vexp(const V& x) { return vmap(x, [](double y) { return fexp(y); }); }
+template <class V>
+__device__ inline V vlog10(const V& x) { return vmap(x, [](double y) { return log10(y); }); }
+
+// Pressure modification c of a falloff reaction and its derivatives by [M] and
+// T; adjoint: Pr dc/dPr at fixed [M] and the factor qA (dq/d ln A = q qA - R Pr dc/dPr).
+template <bool EXT, int MODE, class V>
+__device__ __forceinline__ void falloff(const FallRec& fr_, int kind, uint32_t cm, bool chemact, const V& T, const V& invT,
+                                        const V& lnT, const V& lnkf, double bexp, double th, const V& M, V& c, V& dcdM,
+                                        V& dcdT, V& Pr_dcdPr, V& qA) {
+    constexpr bool DER = MODE != GM_SRC, ADJ = MODE == GM_ADJ;
+    const V rk = vexp(fr_.lnA0 + fr_.b0 * lnT - fr_.theta0 * invT - lnkf);     // k0 / k_inf
+    const V Pr = M * rk;
+    V F = 1.0, dlF_dlP = 0.0, dlF_dT = 0.0;
+    if (kind == K_TROE) {
+        const double al = fr_.p[0], i3 = fr_.p[1], i1 = fr_.p[2], t2 = fr_.p[3];
+        const V e3 = vexp(-T * i3), e1x = vexp(-T * i1), e2 = vexp(-t2 * invT);
+        const V Fc = (1.0 - al) * e3 + al * e1x + e2;
+        const V lf = vlog10(Fc);
+        const V cc = -0.4 - 0.67 * lf;
+        const V nn = 0.75 - 1.27 * lf;
+        const V Aa = vlog10(Pr) + cc;
+        const V Bd = nn - 0.14 * Aa;
+        const V f = Aa / Bd;
+        const V den = 1.0 + f * f;
+        const V lF = lf / den;
+        F = vexp(LN10 * lF);
+        if (DER) {
+            const V gg = -2.0 * lf * f / (den * den);
+            dlF_dlP = gg * nn / (Bd * Bd);
+            const V df_dL = (-0.67 * Bd + 1.1762 * Aa) / (Bd * Bd);
+            const V dlF_dL = 1.0 / den + gg * df_dL;
+            const V dFc = -(1.0 - al) * i3 * e3 - al * i1 * e1x + t2 * invT * invT * e2;
+            dlF_dT = dlF_dL * dFc / (Fc * LN10);
+        }
+    } else if (EXT && (cm & CHUNK_SRI) && kind == K_SRI) {
+        const double a = fr_.p[0], bb = fr_.p[1], ic = fr_.p[2], ee = fr_.p[4];
+        const V lP = vlog10(Pr);
+        const V Xs = 1.0 / (1.0 + lP * lP);
+        const V eb = vexp(-bb * invT), ec = vexp(-T * ic);
+        const V base = a * eb + ec;
+        const V lb = vlog10(base);
+        const V lF = fr_.p[3] + Xs * lb + ee * lnT * (1.0 / LN10);
+        F = vexp(LN10 * lF);
+        if (DER) {
+            dlF_dlP = -2.0 * lb * lP * Xs * Xs;
+            const V dbase = a * bb * invT * invT * eb - ic * ec;
+            dlF_dT = (Xs * dbase / base + ee * invT) * (1.0 / LN10);
+        }
+    }
+    const V ip = 1.0 / (1.0 + Pr);
+    const bool chem = EXT && (cm & CHUNK_CHEMACT) && chemact;
+    c = chem ? F * rk * ip : F * Pr * ip;
+    if (DER) {
+        const V dlnPr = (fr_.b0 + fr_.theta0 * invT) * invT - (bexp + th * invT) * invT;
+        if (!chem) {
+            const V dc_dPr = F * ip * ip + F * ip * dlF_dlP;
+            dcdM = dc_dPr * rk;
+            if (ADJ) Pr_dcdPr = Pr * dc_dPr;
+            dcdT = dc_dPr * Pr * dlnPr + c * LN10 * dlF_dT;
+        } else {
+            dcdM = c * (dlF_dlP / M - rk * ip);
+            dcdT = c * (ip + dlF_dlP) * dlnPr + c * LN10 * dlF_dT;
+            if (ADJ) qA = Pr * ip - dlF_dlP;
+        }
+    }
 }
 
 // a value that all lanes hold, in scalar registers
@@ -269,12 +349,6 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     auto PO = [&](int i) -> V& { return vec(pool, i); };
     auto SP = [&](int k, int f) -> V& { return vec(A + f * (ns + 1) * NV, k); };
     auto K = [&](int q) { return vec(SC, q); };
-    auto vmap = [](auto x, auto f) {
-#pragma unroll
-        for (int v = 0; v < (int)(sizeof(x) / 8); ++v) x[v] = f(x[v]);
-        return x;
-    };
-    auto vexp = [&](const auto& x) { return vmap(x, [](double y) { return fexp(y); }); };
     auto vclamp = [&](const auto& x) { return vmap(x, [](double y) { return clamp_c(y); }); };
     // the reactions of a Jacobian hold too much in registers for several
     // states: there each wave works for one, state rst
@@ -638,62 +712,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                     for (int k = 0; k < 4; ++k) u.v[k] = at4(q, (uint32_t)p * 4u + k);
                     fr_ = u.f;
                 }
-                const V rk = vexp(fr_.lnA0 + fr_.b0 * lnT - fr_.theta0 * invT - lnkf);     // k0 / k_inf
-                const V Pr = M * rk;
-                V F = 1.0, dlF_dlP = 0.0, dlF_dT = 0.0;
-                auto vlog10 = [&](const V& x) { return vmap(x, [](double y) { return log10(y); }); };
-                if (kind == K_TROE) {
-                    const double al = fr_.p[0], i3 = fr_.p[1], i1 = fr_.p[2], t2 = fr_.p[3];
-                    const V e3 = vexp(-T * i3), e1x = vexp(-T * i1), e2 = vexp(-t2 * invT);
-                    const V Fc = (1.0 - al) * e3 + al * e1x + e2;
-                    const V lf = vlog10(Fc);
-                    const V cc = -0.4 - 0.67 * lf;
-                    const V nn = 0.75 - 1.27 * lf;
-                    const V Aa = vlog10(Pr) + cc;
-                    const V Bd = nn - 0.14 * Aa;
-                    const V f = Aa / Bd;
-                    const V den = 1.0 + f * f;
-                    const V lF = lf / den;
-                    F = vexp(LN10 * lF);
-                    if (DER) {
-                        const V gg = -2.0 * lf * f / (den * den);
-                        dlF_dlP = gg * nn / (Bd * Bd);
-                        const V df_dL = (-0.67 * Bd + 1.1762 * Aa) / (Bd * Bd);
-                        const V dlF_dL = 1.0 / den + gg * df_dL;
-                        const V dFc = -(1.0 - al) * i3 * e3 - al * i1 * e1x + t2 * invT * invT * e2;
-                        dlF_dT = dlF_dL * dFc / (Fc * LN10);
-                    }
-                } else if (EXT && (cm & CHUNK_SRI) && kind == K_SRI) {
-                    const double a = fr_.p[0], bb = fr_.p[1], ic = fr_.p[2], ee = fr_.p[4];
-                    const V lP = vlog10(Pr);
-                    const V Xs = 1.0 / (1.0 + lP * lP);
-                    const V eb = vexp(-bb * invT), ec = vexp(-T * ic);
-                    const V base = a * eb + ec;
-                    const V lb = vlog10(base);
-                    const V lF = fr_.p[3] + Xs * lb + ee * lnT * (1.0 / LN10);
-                    F = vexp(LN10 * lF);
-                    if (DER) {
-                        dlF_dlP = -2.0 * lb * lP * Xs * Xs;
-                        const V dbase = a * bb * invT * invT * eb - ic * ec;
-                        dlF_dT = (Xs * dbase / base + ee * invT) * (1.0 / LN10);
-                    }
-                }
-                const V ip = 1.0 / (1.0 + Pr);
-                const bool chemact = EXT && (cm & CHUNK_CHEMACT) && (w & GI_CHEMACT);
-                c = chemact ? F * rk * ip : F * Pr * ip;
-                if (DER) {
-                    const V dlnPr = (fr_.b0 + fr_.theta0 * invT) * invT - (bexp + th * invT) * invT;
-                    if (!chemact) {
-                        const V dc_dPr = F * ip * ip + F * ip * dlF_dlP;
-                        dcdM = dc_dPr * rk;
-                        if (ADJ) Pr_dcdPr = Pr * dc_dPr;
-                        dcdT = dc_dPr * Pr * dlnPr + c * LN10 * dlF_dT;
-                    } else {
-                        dcdM = c * (dlF_dlP / M - rk * ip);
-                        dcdT = c * (ip + dlF_dlP) * dlnPr + c * LN10 * dlF_dT;
-                        if (ADJ) qA = Pr * ip - dlF_dlP;
-                    }
-                }
+                falloff<EXT, MODE>(fr_, kind, cm, (w & GI_CHEMACT) != 0, T, invT, lnT, lnkf, bexp, th, M, c, dcdM, dcdT, Pr_dcdPr, qA);
             }
             const V q = PLAIN ? R : c * R;
             if constexpr (!DER) {

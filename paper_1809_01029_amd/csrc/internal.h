@@ -166,7 +166,7 @@ struct DevMech {
 // two slots, so that every slot has coefficient 1 (at most three a side).
 struct alignas(16) FastRec {         // 64 B
     uint32_t info;                   // GI_*
-    uint32_t pad;
+    uint32_t orig;                   // description index
     uint32_t chunk;                  // as RxnRec::chunk, of the single-molecule slots
     uint16_t sp[6];                  // species of slot a (Ns = empty)
     uint16_t bpos;                   // pool element of the reverse rate (reversible)
@@ -221,7 +221,8 @@ struct GatherMech {
     // an empty one, then in their place q of each and dE of each, then the
     // output buffer
     int zero, b3, npool;
-    int n_rounds, pad;
+    int n_rounds;
+    int nfall;                       // reactions p < nfall have a falloff record
     int neff;                        // reactions p < neff have the FastEff p + 1, the others 0
     int dshift;                      // entry word: position | column << 16 | dense row + 1 << dshift
     const PJ_GLOBAL ThermoRec* th;
@@ -364,6 +365,10 @@ struct GatherCall {
 };
 hipError_t launch_gather(const GatherCall& c);
 hipError_t launch_gather_ext(const GatherCall& c);
+// wide.hip, wide_ext.hip (wide_body.h)
+int64_t wide_lds(const GatherMech& gm, int waves);
+hipError_t launch_wide(const GatherCall& c);
+hipError_t launch_wide_ext(const GatherCall& c);
 
 // kernels.hip (kernel_body.h)
 enum Mode : int { MODE_SRC = 0, MODE_SPARSE = 1, MODE_DENSE = 2, MODE_ADJ = 3,

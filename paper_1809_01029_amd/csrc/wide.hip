@@ -1,0 +1,11 @@
+// Wide kernels for mechanisms of the default reaction types, their LDS sizing,
+// and the dispatch to the further types' (wide_ext.hip).
+#include "wide_body.h"
+
+namespace pj {
+
+int64_t wide_lds(const GatherMech& gm, int waves) { return wide_doubles(gm.ns, 2 * waves) * 8; }
+
+hipError_t launch_wide(const GatherCall& c) { return c.ext ? launch_wide_ext(c) : launch_wide_impl<false>(c); }
+
+}  // namespace pj
