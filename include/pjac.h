@@ -331,8 +331,10 @@ int64_t pj_mech_lds_bytes(const pj_mech* mech, int for_jacobian);
  * NULL batch, a bad mode or segment index), so that segments of smaller
  * mechanisms hold more states at once.  Per mode, the batch can instead run
  * one launch per segment, each at its mechanism's own launch shape for that
- * mode (pj_batch_set_strategy(batch, mode, 1); 0 = the persistent launch,
- * the default); the graph then holds those launches.
+ * mode (pj_batch_set_strategy(batch, mode, 1); 0 = the persistent launch); the
+ * graph then holds those launches.  Until one is set, source terms and sparse
+ * Jacobians of mechanisms at their automatic launch shapes take whichever is
+ * the faster for their sizes, the rest the persistent launch.
  *
  * pj_batch_add records a segment (n_states may be 0); adding or clearing
  * segments, or changing the launch shape, discards a captured graph.
@@ -345,7 +347,7 @@ int64_t pj_mech_lds_bytes(const pj_mech* mech, int for_jacobian);
  * fastest for that mode: *states_per_group and *waves_per_group receive 0
  * when the per-segment launches win (the best persistent shape is kept as
  * the mode's launch shape either way).  pj_batch_strategy returns the mode's
- * strategy (0 or 1; -1 for a NULL batch or a bad mode).  Errors as for the
+ * strategy as set (0 or 1; 0 while none is; -1 for a NULL batch or a bad mode).  Errors as for the
  * per-mechanism calls, with the segment index in the message
  * (pj_batch_last_error).
  */

@@ -246,10 +246,32 @@ pj_status enqueue_segments(pj_batch* b, int mode, pj_form form, pj_layout layout
     return PJ_OK;
 }
 
+// One launch per segment: as set, else (-1) where that is faster and neither
+// the batch nor a mechanism has a launch shape set: the mechanisms' automatic
+// kernels gain more than the launches and their tails cost.  Segments of 13, 53
+// and 111 species, persistent launch -> launch per segment, us: source terms of
+// 3000 + 70000 + 20000 states 495 -> 344, of 50 each 129 -> 24, of 64 segments
+// of 100 states 2679 -> 504; sparse Jacobians of these 2295 -> 1881, 102 -> 57,
+// 2146 -> 1204, of 50 + 5000 + 500 states 152 -> 149; in layout F these last
+// 153 -> 164, of 2000 each 159 -> 167, 3000 + 70000 + 20000 2408 -> 2140, 500
+// each 107 -> 80.  (Adjoint segments may share a parameter-sum buffer, which a
+// launch of its own would clear.)
+bool per_segment(const pj_batch* b, int mode, pj_layout layout) {
+    if (b->per_seg[mode] >= 0) return b->per_seg[mode] == 1;
+    if (mode == pj::MODE_ADJ || b->user_S[mode] || b->user_W[mode]) return false;
+    int64_t n = 0;
+    for (auto& sg : b->segs) {
+        if (!sg.mech->m.automatic[mode] || !sg.mech->m.gm.ok || sg.mech->m.dm.det || sg.mech->m.dm.lsearch) return false;
+        n += sg.n;
+    }
+    return n > 0 && (mode == pj::MODE_SRC || layout == PJ_LAYOUT_C || n <= 3072 || n >= 32768);
+}
+
 // the batch as configured for the mode: one persistent launch of shape S x W,
 // or one launch per segment
 pj_status enqueue_mode(pj_batch* b, int mode, pj_form form, pj_layout layout, int S, int W, hipStream_t st) {
-    return b->per_seg[mode] ? enqueue_segments(b, mode, form, layout, st) : enqueue(b, mode, form, layout, S, W, st);
+    return per_segment(b, mode, layout) ? enqueue_segments(b, mode, form, layout, st)
+                                        : enqueue(b, mode, form, layout, S, W, st);
 }
 
 }  // namespace
@@ -360,7 +382,7 @@ pj_status pj_batch_set_strategy(pj_batch* b, int mode, int per_segment) {
 
 int pj_batch_strategy(const pj_batch* b, int mode) {
     if (!b || !batch_mode(mode)) return -1;
-    return b->per_seg[mode];
+    return b->per_seg[mode] == 1;
 }
 
 pj_status pj_batch_eval(pj_batch* b, int mode, pj_form form, pj_layout layout, pj_stream stream) {
@@ -370,7 +392,7 @@ pj_status pj_batch_eval(pj_batch* b, int mode, pj_form form, pj_layout layout, p
     if (b->segs.empty()) { g_err.clear(); return PJ_OK; }
     int S, W;
     batch_shape(b, mode, S, W);
-    if (!b->per_seg[mode] && batch_lds(b, mode, S, W) > lds_max_of(b))
+    if (b->per_seg[mode] != 1 && batch_lds(b, mode, S, W) > lds_max_of(b))
         return fail(PJ_E_UNSUPPORTED, "a segment's working set exceeds the LDS of one workgroup");
     r = enqueue_mode(b, mode, form, layout, S, W, (hipStream_t)stream);
     if (r == PJ_OK) g_err.clear();
@@ -384,8 +406,8 @@ pj_status pj_batch_eval_graph(pj_batch* b, int mode, pj_form form, pj_layout lay
     if (b->segs.empty()) { g_err.clear(); return PJ_OK; }
     int S, W;
     batch_shape(b, mode, S, W);
-    const int ps = b->per_seg[mode];
-    if (!ps && batch_lds(b, mode, S, W) > lds_max_of(b))
+    const int ps = per_segment(b, mode, layout);
+    if (b->per_seg[mode] != 1 && batch_lds(b, mode, S, W) > lds_max_of(b))
         return fail(PJ_E_UNSUPPORTED, "a segment's working set exceeds the LDS of one workgroup");
     if (!b->exec || b->g_mode != mode || b->g_form != form || b->g_layout != layout || b->g_S != S || b->g_W != W ||
         b->g_per_seg != ps) {

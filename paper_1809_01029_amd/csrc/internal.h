@@ -452,7 +452,7 @@ struct pj_batch {
     std::vector<Seg> segs;
     int device = -1;
     int user_S[pj::N_MODES] = {0, 0, 0, 0}, user_W[pj::N_MODES] = {0, 0, 0, 0};
-    int per_seg[pj::N_MODES] = {0, 0, 0, 0};   // 1: one launch per segment
+    int per_seg[pj::N_MODES] = {-1, -1, -1, -1};   // 1: one launch per segment, 0: one launch, -1: automatic
     // device copy of the segment table, for the shape it was built with
     pj::BatchSeg* d_segs = nullptr;
     size_t d_cap = 0;

@@ -167,3 +167,34 @@ def test_gather_adjoint(torch_cuda, api, case, form, layout, shape, mech_dir):
     # bound: every entry's own, and the rounding of the sum of N products
     so = np.einsum("sij,si->sj", S, np.abs(v)) + J.shape[1] * 2.3e-16 * np.einsum("sij,si->sj", np.abs(J), np.abs(v))
     check_jac(host(j), jo, so, "approximate J^T v")
+
+
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("mode,layout", [("source", "C"), ("source", "F"), ("sparse", "C"), ("sparse", "F")])
+@pytest.mark.parametrize("sizes", [(1, 0, 3), (1025, 1024, 1023), (1025, 1024, 1024)])
+def test_batch_automatic_strategy(torch_cuda, api, sizes, mode, layout, graph, mech_dir):
+    """A batch with no strategy set, either side of its choice's line, against
+    the persistent launch: 1e-12 of a state's largest value, as above."""
+    torch = torch_cuda
+    b = api.Batch()
+    segs = []
+    for name, n in zip(("ns13", "ns53", "tiny"), sizes):
+        m, path = tiny_file(3, mech_dir) if name == "tiny" else workload_file(name, mech_dir)
+        x, p = synth.pack_state(synth.make_states(m, n, 2), "conp", layout)
+        mech = api.load_mechanism(path)
+        x, p = torch.from_numpy(np.ascontiguousarray(x)).cuda(), torch.from_numpy(p.copy()).cuda()
+        out = torch.zeros((n, mech.nnz) if layout == "C" else (mech.nnz, n), dtype=torch.float64, device="cuda")
+        segs.append((out, torch.zeros_like(x)))
+        b.add(mech, x, p, layout, out=out, dstate=segs[-1][1])
+    got = []
+    for k in range(3):
+        if k == 2:
+            b.set_strategy(mode, False)
+        b.eval(mode, "conp", layout, graph=graph)
+        torch.cuda.synchronize()
+        got.append([[t.clone() if layout == "C" else t.t().clone() for t in sg] for sg in segs])
+    for first, again, ref in zip(*got):
+        for f, a, r in zip(first, again, ref):
+            if r.shape[0]:
+                scale = r.abs().amax(dim=1, keepdim=True)
+                assert bool(((f - r).abs() <= 1e-12 * scale).all()) and bool(((a - r).abs() <= 1e-12 * scale).all())
