@@ -34,8 +34,10 @@ int lanes_of(size_t deg, int len) {
 // the first word, else into bits 28..30 of the entry word.
 // Sums take 2^k neighbouring lanes, the widest first (so that each is
 // aligned), then the longest, so that the lanes of a group end together.  The
-// length at which a sum is spread over more lanes is the one that gives the
-// fewest steps over all groups, a group's own cost counted as 8.
+// length at which a sum is spread over more lanes is the one with the least
+// cost: the steps of all groups, a group's own cost counted as 8, and the
+// largest share of four waves that take the groups in turn (the others wait for
+// it: 111 species, 262144 states 8.49 ms without that term, 8.35 with it).
 void cut(std::vector<Sum> sums, int bits, bool lp_in_word, uint32_t empty, GatherImage::Lists& out) {
     const int per_word = 32 / bits, head = 3 * per_word, chunk = 4 * per_word;
     int best = -1, full = head + chunk;
@@ -60,9 +62,13 @@ void cut(std::vector<Sum> sums, int bits, bool lp_in_word, uint32_t empty, Gathe
         return gr;
     };
     for (int nc = 1; nc <= 6; ++nc) {
-        int cost = 0;
-        for (auto& q : arrange(head + nc * chunk))
-            cost += 8 + head + std::max(1, (q[2] - head + chunk - 1) / chunk) * chunk;
+        int cost = 0, t = 0, load[4] = {0, 0, 0, 0};
+        for (auto& q : arrange(head + nc * chunk)) {
+            const int c = 8 + head + std::max(1, (q[2] - head + chunk - 1) / chunk) * chunk;
+            cost += c;
+            load[t++ & 3] += c;
+        }
+        cost += 4 * *std::max_element(load, load + 4);
         if (best < 0 || cost < best) {
             best = cost;
             full = head + nc * chunk;

@@ -43,14 +43,16 @@
 // coalesced.
 //
 // Sparse Jacobian of 111 species and 784 reactions, CONP, layout C, 262144
-// states: 8.70 ms against the scatter kernels' 11.21 (4 states and 8 waves a
-// workgroup, the best of their shapes).  About 14,600 vector instructions a
-// state, 75% of the issue slots of the four SIMDs; list words decoded, reads
-// and additions are 60% of them, the reactions 28%; LDS reads take 42% of the
-// compute unit's time, bank conflicts 45% of that.  Writing the output alone
-// takes 1.4 ms at the fill rate.  Four waves a state: the 40 kB of a state let
-// four workgroups share a compute unit, which at 128 registers is all the
-// waves it holds (3 waves 10.1 ms, 8 waves 12.6; two states with 8 waves 9.0).
+// states: 8.35 ms against the scatter kernels' 11.21 (4 states and 8 waves a
+// workgroup, the best of their shapes).  About 13,500 vector instructions a
+// state, 70% of the issue slots of the four SIMDs: list words decoded, reads and
+// additions are 60% of them, the reactions 30%; LDS reads take 43% of the compute
+// unit's time, bank conflicts 45% of that.  Writing the output alone takes 1.4
+// ms at the fill rate.  Four waves a state: the 40 kB of a state let four
+// workgroups share a compute unit, which at 128 registers is all the waves it
+// holds (3 waves 10.1 ms, 8 waves 12.6; two states with 8 waves 9.2).  Lists
+// sorted so that all lanes of a group add or subtract together save a tenth of
+// the instructions, but what they are padded with costs more reads: 8.9 ms.
 #pragma once
 
 #include <type_traits>
@@ -70,9 +72,13 @@ namespace {
 enum { SC_LNT = 0, SC_NSUM, SC_CB, SC_ICB, SC_DP, SC_DDP, SC_TT, SC_TS, SC_ST, SC_SS, SC_TDOT, SC_SDOT, SC_OM, SC_SCW,
        SC_T, SC_V, SC_P, SC_INVT, SC_INVV, SC_INVRT, SC_CTOT, SC_LNP,
        SC_KAP, SC_VT, SC_VS, SC_LB, SC_N };
-// fields of a species record in LDS: {exp g, C, exp -g, h}, after the
-// reactions {wdot, 1/C, T column sum, h}
-enum { A_E = 0, A_C = 1, A_I = 2, A_H = 3, A_W = 0, A_IC = 1, A_VT = 2 };
+// fields of a species record in LDS: {exp g, C, exp -g, h, chat/R}, after the
+// reactions {wdot, 1/C, T column sum, h, chat/R}; the adjoint's also {what a unit
+// of wdot_k adds to v . f, v of its row}.  The adjoint, which reads six of a
+// species at once, keeps them together, an odd number apart (one address; 111
+// species, 262144 states 5.83 ms against 5.93 with an array per field); the
+// Jacobian, whose lists read single fields, an array each (8.65 ms against 9.28).
+enum { A_E = 0, A_C = 1, A_I = 2, A_H = 3, A_CP = 4, A_Y = 5, A_VV = 6, A_W = 0, A_IC = 1, A_VT = 2 };
 constexpr double C_TINY = 1e-150;
 constexpr double G_MIN = -160.0, G_MAX = 60.0;
 constexpr double LNK_MIN = -690.0;
@@ -331,13 +337,12 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     // (the adjoint: without the elements from b3 on)
     const int npool = JAC ? gmp->npool : ADJ ? gmp->b3 : ((nr + 2) & ~1);
     double* const A = pool + npool * NV;
-    double* const CP = A + 4 * (ns + 1) * NV;
-    double* const VS = CP + (ns + 1) * NV;          // V/P column sums; before them dCp/dT
+    constexpr int AS = ADJ ? 7 : 5;                 // fields of a species
+    auto fld = [&](int k, int f) { return ADJ ? k * AS + f : f * (ns + 1) + k; };
+    double* const VS = A + AS * (ns + 1) * NV;      // V/P column sums; before them dCp/dT
     double* const TQ = VS + (DER ? (ns + 1) * NV : 0);
-    double* const SQ = TQ + (DER ? (ns + 1) * NV : 0);
-    double* const Y = TQ;                           // adjoint: what a unit of wdot_k adds to v . f
-    double* const VV = SQ;                          // adjoint: v of the species rows
-    double* const BB = SQ + (DER ? (ns + 1) * NV : 0);
+    double* const SQ = TQ + (JAC ? (ns + 1) * NV : 0);
+    double* const BB = SQ + (JAC ? (ns + 1) * NV : 0);
     double* const PW = BB + (JAC ? (gmp->n_dense_rows + 1) * NV : 0);
     double* const SC = PW + 7 * NV;
     constexpr int NRS = ADJ ? 7 : JAC ? 4 : 0;      // the waves' sums over reactions
@@ -347,7 +352,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     typedef __attribute__((address_space(3))) V LV;
     auto vec = [](double* p, int i) -> V& { return *reinterpret_cast<V*>(p + i * NV); };
     auto PO = [&](int i) -> V& { return vec(pool, i); };
-    auto SP = [&](int k, int f) -> V& { return vec(A + f * (ns + 1) * NV, k); };
+    auto SP = [&](int k, int f) -> V& { return vec(A, fld(k, f)); };
     auto K = [&](int q) { return vec(SC, q); };
     auto vclamp = [&](const auto& x) { return vmap(x, [](double y) { return clamp_c(y); }); };
     // the reactions of a Jacobian hold too much in registers for several
@@ -422,11 +427,11 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         odd_c |= !(fabs(cb) >= C_TINY);
         if (lane < NV) {
             auto put = [&](double* p, int i, double x) { p[i * NV + lane] = x; };
-            put(A, A_C * (ns + 1) + bath, cb);
-            put(A, A_E * (ns + 1) + ns, 1.0);
-            put(A, A_C * (ns + 1) + ns, 1.0);
-            put(A, A_I * (ns + 1) + ns, 1.0);
-            put(A, A_H * (ns + 1) + ns, 0.0);
+            put(A, fld(bath, A_C), cb);
+            put(A, fld(ns, A_E), 1.0);
+            put(A, fld(ns, A_C), 1.0);
+            put(A, fld(ns, A_I), 1.0);
+            put(A, fld(ns, A_H), 0.0);
             put(SC, SC_NSUM, nsum);
             put(SC, SC_CB, cb);
             put(SC, SC_ICB, 1.0 / clamp_c(cb));
@@ -454,9 +459,9 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 put(SC, SC_VT, wt);
                 put(SC, SC_VS, ws);
                 put(pool, gmp->zero, 0.0);
-                put(CP, ns, 0.0);
-                put(Y, ns, 0.0);
-                put(VV, ns, 0.0);
+                put(A, fld(ns, A_CP), 0.0);
+                put(A, fld(ns, A_Y), 0.0);
+                put(A, fld(ns, A_VV), 0.0);
             } else {
                 put(pool, nr, 0.0);
             }
@@ -484,7 +489,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             if (!logs && k < ns - 1) {
                 const double c = X(sc, 2 + k) / (FORM == PJ_CONP ? X(sc, 1) : param[sc]);
                 odd_c |= !(fabs(c) >= C_TINY);
-                A[(A_C * (ns + 1) + k) * NV + v] = c;
+                A[fld(k, A_C) * NV + v] = c;
             }
             const double lnT = log(T), invT = 1.0 / T;
             if (k == 0) SC[SC_LNT * NV + v] = lnT;
@@ -496,15 +501,15 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             const double g = h - sr;
             odd_g |= !(g >= G_MIN && g <= G_MAX);
             if (logs) {
-                A[(A_E * (ns + 1) + k) * NV + v] = g;
+                A[fld(k, A_E) * NV + v] = g;
                 if (k == 0) SC[SC_LNP * NV + v] = log(PREF / (RU * T));
             } else {
                 const double e = fexp(g);
-                A[(A_E * (ns + 1) + k) * NV + v] = e;
-                A[(A_I * (ns + 1) + k) * NV + v] = 1.0 / e;
-                A[(A_H * (ns + 1) + k) * NV + v] = h;
-                CP[k * NV + v] = FORM == PJ_CONP ? cp : cp - 1.0;
-                if (ADJ) VV[k * NV + v] = k < ns - 1 ? layout == PJ_LAYOUT_F ? vin[(2 + k) * (long)n + sc] : vin[sc * (long)N + 2 + k] : 0.0;
+                A[fld(k, A_E) * NV + v] = e;
+                A[fld(k, A_I) * NV + v] = 1.0 / e;
+                A[fld(k, A_H) * NV + v] = h;
+                A[fld(k, A_CP) * NV + v] = FORM == PJ_CONP ? cp : cp - 1.0;
+                if (ADJ) A[fld(k, A_VV) * NV + v] = k < ns - 1 ? layout == PJ_LAYOUT_F ? vin[(2 + k) * (long)n + sc] : vin[sc * (long)N + 2 + k] : 0.0;
                 if (DER) VS[k * NV + v] = a1 + T * (a(14) + T * (a(15) + T * a(16)));
             }
         }
@@ -522,7 +527,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     if (logs) {
         // some g out of range: exponentials of the sums, from g itself
         if (tid >= tb) thermo(true);
-        if (tid < NV) A[(A_E * (ns + 1) + ns) * NV + tid] = 0.0;
+        if (tid < NV) A[fld(ns, A_E) * NV + tid] = 0.0;
         __syncthreads();
     }
 
@@ -531,7 +536,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     if constexpr (ADJ) {
         const GatherPtr gm = fresh(gmp);
         V d0 = 0.0;
-        for (int k = lane; k < ns; k += 64) d0 += SP(k, A_C) * vec(CP, k);
+        for (int k = lane; k < ns; k += 64) d0 += SP(k, A_C) * SP(k, A_CP);
         const V Dp = vmap(d0, [](double x) { return wave_total(x); });
         if (wave == 0 && lane == 0) vec(SC, SC_DP) = Dp;
         for (int it = tid; it < ns * NV; it += nthr) {
@@ -540,8 +545,8 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             const double T = C_(SC_T), Vv = C_(SC_V), P = C_(SC_P), vT = C_(SC_VT), vS = C_(SC_VS);
             const double a = -(vT + vS * (FORM == PJ_CONP ? Vv : P) * C_(SC_INVT)) / (NV == 1 ? Dp[0] : Dp[v]);
             const double b = vS * RU * T * (FORM == PJ_CONP ? Vv / P : 1.0);
-            const double h = A[(A_H * (ns + 1) + k) * NV + v];
-            Y[k * NV + v] = Vv * VV[k * NV + v] + (a * T) * (FORM == PJ_CONP ? h : h - 1.0) + b * at(gm->wfac, (uint32_t)k);
+            const double h = A[fld(k, A_H) * NV + v];
+            A[fld(k, A_Y) * NV + v] = Vv * A[fld(k, A_VV) * NV + v] + (a * T) * (FORM == PJ_CONP ? h : h - 1.0) + b * at(gm->wfac, (uint32_t)k);
             if (k == 0) SC[SC_KAP * NV + v] = a;
         }
         __syncthreads();
@@ -552,7 +557,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         V d0 = 0.0, d1 = 0.0;   // D' = sum C chat/R, dD'/dT = sum C dCp/R/dT
         for (int k = lane; k < ns; k += 64) {
             const V c = SP(k, A_C);
-            d0 += c * vec(CP, k);
+            d0 += c * SP(k, A_CP);
             if (DER) d1 += c * vec(VS, k);
         }
         d0 = vmap(d0, [](double x) { return wave_total(x); });
@@ -570,7 +575,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         typedef RV V;
         auto vec = rvec;
         auto PO = [&](int i) -> V& { return vec(pool, i); };
-        auto SP = [&](int k, int f) -> V& { return vec(A + f * (ns + 1) * NV, k); };
+        auto SP = [&](int k, int f) -> V& { return vec(A, fld(k, f)); };
         auto K = [&](int q) { return vec(SC, q); };
         auto U = [&](int q) { return RN == 1 ? vmap(K(q), [](double x) { return uniform(x); }) : K(q); };
         const V T = U(SC_T), lnT = U(SC_LNT), invT = U(SC_INVT), Ctot = U(SC_CTOT);
@@ -656,9 +661,9 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                     xa[a][0] = xa[a][1] = xa[a][2] = 0.0;
                     if ((cm >> a) & 1) {
                         const int k = rr.sp[a];
-                        xa[a][0] = vec(Y, k);
-                        xa[a][1] = vec(CP, k);
-                        if (FORM == PJ_CONP) xa[a][2] = vec(VV, k);
+                        xa[a][0] = SP(k, A_Y);
+                        xa[a][1] = SP(k, A_CP);
+                        if (FORM == PJ_CONP) xa[a][2] = SP(k, A_VV);
                     }
                 }
                 PJ_READS_FIRST();
@@ -836,9 +841,13 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         k.d = make_uint2(0, 0);
         return k;
     };
+    // (a task's descriptor is the wave's: told to the compiler, which has it in
+    // vector registers once it has been through the loop)
+    auto desc_x = [](const Task& k) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)k.d.x); };
+    auto desc_y = [](const Task& k) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)k.d.y); };
     auto task_of = [&](const Task& k, int& most, int& nm, bool& first, int& lp, int& what) {
-        most = (int)(k.d.x & 0xFF);
-        nm = (int)(k.d.x >> 8);
+        most = (int)(desc_x(k) & 0xFF);
+        nm = (int)(desc_x(k) >> 8);
         // the first lane of a sum names it; the others hold all ones, which as
         // a number of lanes lets every level add: they are not read
         first = k.h.x != 0xFFFFFFFFu;
@@ -863,7 +872,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         words(k.x.y, k.x.z);
         words(k.x.w, none);
         for (int c = 0; c < nm; ++c) {
-            const uint4 y = at4(l.more, (k.d.y + c) * 64 + lane);
+            const uint4 y = at4(l.more, (desc_y(k) + c) * 64 + lane);
             words(y.x, y.y);
             words(y.z, y.w);
         }
@@ -883,7 +892,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 for (int w = 0; w < rnw; ++w) t[c] += vec(RS, NRS * w + c);
             }
             const V T = K(SC_T), Vv = K(SC_V), P = K(SC_P), iT = K(SC_INVT), iV = K(SC_INVV), ct = K(SC_CTOT), Dp = K(SC_DP);
-            const V kap = K(SC_KAP), vS = K(SC_VS), cpb = vec(CP, bath);
+            const V kap = K(SC_KAP), vS = K(SC_VS), cpb = SP(bath, A_CP);
             const V Tdot = -T * t[3] / Dp, Om = t[4];
             const V dDdT = K(SC_DDP) - cpb * ct * iT;
             const V dDdS = FORM == PJ_CONP ? -((Dp - cpb * K(SC_CB)) - cpb * (K(SC_NSUM) * iV)) * iV : cpb / (RU * T);
@@ -919,7 +928,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             const uint32_t hw[7] = {k.h.y, k.h.z, k.h.w, k.x.x, k.x.y, k.x.z, k.x.w};
             words(hw, std::integral_constant<int, 7>());
             for (int c = 0; c < nm; ++c) {
-                const uint4 y = at4(gm->cl.more, (k.d.y + c) * 64 + lane);
+                const uint4 y = at4(gm->cl.more, (desc_y(k) + c) * 64 + lane);
                 const uint32_t x[4] = {y.x, y.y, y.z, y.w};
                 words(x, std::integral_constant<int, 4>());
             }
@@ -935,8 +944,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             auto C_ = [&](int q) { return SC[q * NV + s2]; };
             const double lb = C_(SC_LB), kt = C_(SC_KAP), cpb = C_(SC_CB), iV = C_(SC_INVV);
             for (int i = g2; i < N; i += G) {
-                const int k = (i - 2) * NV + s2;
-                const double y = i == 0 ? C_(SC_TT) : i == 1 ? C_(SC_TS) : iV * (A[k] - lb) + kt * (CP[k] - cpb);
+                const double y = i == 0 ? C_(SC_TT) : i == 1 ? C_(SC_TS) : iV * (A[fld(i - 2, A_E)] - lb) + kt * (A[fld(i - 2, A_CP)] - cpb);
                 if (layout == PJ_LAYOUT_F) jac[(long)i * n + st2] = y;
                 else jac[st2 * (long)N + i] = y;
             }
@@ -984,7 +992,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 auto four = [&](const uint4& y) { two(y.x), two(y.y), two(y.z), two(y.w); };
                 two(k.h.y), two(k.h.z), two(k.h.w);
                 four(k.x);
-                for (int c = 0; c < nm; ++c) four(at4(gm->bl.more, (k.d.y + c) * 64 + lane));
+                for (int c = 0; c < nm; ++c) four(at4(gm->bl.more, (desc_y(k) + c) * 64 + lane));
                 w0 = folded(w0);
                 if (first) vec(BB, 1 + what) = w0;
             }
@@ -1047,7 +1055,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                     const uint32_t x[4] = {y.x, y.y, y.z, y.w};
                     words(x, std::integral_constant<int, 4>());
                 };
-                for (int c = 0; c < nm; ++c) four(at4(gm->cl.more, (k.d.y + c) * 64 + lane));
+                for (int c = 0; c < nm; ++c) four(at4(gm->cl.more, (desc_y(k) + c) * 64 + lane));
                 w0 = folded(w0);
                 w1 = folded(w1);
                 if (first) {
@@ -1077,7 +1085,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             const V wk = SP(k, A_W), h = SP(k, A_H);
             np += (FORM == PJ_CONP ? h : h - 1.0) * wk;
             om += at(gm->wfac, (uint32_t)k) * wk;
-            if (JAC) scw += vec(CP, k) * wk;
+            if (JAC) scw += SP(k, A_CP) * wk;
         }
         auto all = [&](const V& x) { return vmap(x, [](double y) { return wave_total(y); }); };
         np = all(np);
@@ -1111,7 +1119,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         if (!dstate || st2 >= n) return;
         const double V2 = C_(SC_V);
         for (int i = g2; i < N; i += G) {
-            const double v = i < 2 ? C_(i == 0 ? SC_TDOT : SC_SDOT) : V2 * A[(A_W * (ns + 1) + i - 2) * NV + s2];
+            const double v = i < 2 ? C_(i == 0 ? SC_TDOT : SC_SDOT) : V2 * A[fld(i - 2, A_W) * NV + s2];
             if (layout == PJ_LAYOUT_F) dstate[(long)i * n + st2] = v;
             else dstate[st2 * (long)N + i] = v;
         }
@@ -1142,7 +1150,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         for (int t = R.heavy0 + wave; t < R.heavy1; t += nwave) {
             const Task k = hv;
             if (t + nwave < R.heavy1) hv = list_at(gm->jh, t + nwave);
-            const int most = (int)(k.d.x & 0xFF), nm = (int)(k.d.x >> 8);
+            const int most = (int)(desc_x(k) & 0xFF), nm = (int)(desc_x(k) >> 8);
             const int lp = (int)((k.h.y >> 1 & 3) | (k.h.y >> 15 & 4));
             V w0 = 0.0, w1 = 0.0;
             auto words = [&](const uint32_t* x, auto nw) {
@@ -1164,7 +1172,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             const uint32_t x[7] = {k.h.y, k.h.z, k.h.w, k.x.x, k.x.y, k.x.z, k.x.w};
             words(x, std::integral_constant<int, 7>());
             for (int c = 0; c < nm; ++c) {
-                const uint4 y = at4(gm->jh.more, (k.d.y + c) * 64 + lane);
+                const uint4 y = at4(gm->jh.more, (desc_y(k) + c) * 64 + lane);
                 const uint32_t z[4] = {y.x, y.y, y.z, y.w};
                 words(z, std::integral_constant<int, 4>());
             }
@@ -1250,7 +1258,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 const double T2 = C_(SC_T), V2 = C_(SC_V), P2 = C_(SC_P);
                 const double iT = C_(SC_INVT), iV = C_(SC_INVV), ct = C_(SC_CTOT);
                 const double Dp = C_(SC_DP), Tdot = C_(SC_TDOT), Om = C_(SC_OM), Scw = C_(SC_SCW);
-                const double cpb = CP[bath * NV + s2];
+                const double cpb = A[fld(bath, A_CP) * NV + s2];
                 const double dDdT = C_(SC_DDP) - cpb * ct * iT;
                 const double dDdS = FORM == PJ_CONP ? -((Dp - cpb * C_(SC_CB)) - cpb * (C_(SC_NSUM) * iV)) * iV
                                                     : cpb / (RU * T2);
@@ -1271,7 +1279,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                                              : Tdot * iT + P2 * iT * j0 + RU * T2 * C_(SC_SS);
                     } else {
                         const int k = (j - 2) * NV + s2;
-                        j0 = -(T2 * (TQ[k] - tqb) + Tdot * (CP[k] - cpb_n)) * iV / Dp;
+                        j0 = -(T2 * (TQ[k] - tqb) + Tdot * (A[fld(j - 2, A_CP) * NV + s2] - cpb_n)) * iV / Dp;
                         j1 = FORM == PJ_CONP ? V2 * iT * j0 + RTP * (SQ[k] - sqb)
                                              : P2 * iT * j0 + RU * T2 * (SQ[k] - sqb) * iV;
                     }
