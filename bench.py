@@ -42,7 +42,11 @@ def log(*a):
 KERNEL_SOURCES = ["paper_1809_01029_amd/csrc/kernel_body.h", "paper_1809_01029_amd/csrc/kernels.hip",
                   "paper_1809_01029_amd/csrc/kernels_ext.hip", "paper_1809_01029_amd/csrc/internal.h",
                   "paper_1809_01029_amd/csrc/mech.cpp", "paper_1809_01029_amd/csrc/api.cpp",
-                  "paper_1809_01029_amd/csrc/kernels_conv.hip", "paper_1809_01029_amd/csrc/kernels_ext_conv.hip"]
+                  "paper_1809_01029_amd/csrc/kernels_conv.hip", "paper_1809_01029_amd/csrc/kernels_ext_conv.hip",
+                  "paper_1809_01029_amd/csrc/gather_body.h", "paper_1809_01029_amd/csrc/gather.cpp",
+                  "paper_1809_01029_amd/csrc/gather.hip", "paper_1809_01029_amd/csrc/gather_ext.hip",
+                  "paper_1809_01029_amd/csrc/wide_body.h", "paper_1809_01029_amd/csrc/wide.hip",
+                  "paper_1809_01029_amd/csrc/wide_ext.hip"]
 
 
 def kernel_sources_sha256():

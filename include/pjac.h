@@ -244,8 +244,8 @@ pj_status pj_mech_get_arrhenius(const pj_mech* mech, double* lnA, double* b, dou
  * depends on the call's states and layout: few states and, for Jacobians,
  * mechanisms of more than 256 reactions take one or two states per workgroup;
  * source terms of many states take 64, or two of large mechanisms;
- * the others the most states, up to 4, whose working set fits the LDS of one
- * workgroup, and enough waves for about 8 resident waves per compute unit.  A
+ * the others the most states, up to 4 (8 in layout F), whose working set fits
+ * the LDS of one workgroup, and enough waves for about 8 resident waves per compute unit.  A
  * states_per_group that does not fit for a mode is ignored for that mode.
  * One or two states with at least 2 waves (a multiple of the states, and for
  * Jacobians one for every 320 reactions of a state) run kernels that add in a
@@ -295,7 +295,9 @@ int pj_mech_dense_unroll(const pj_mech* mech);
  * 2) and are overwritten.  Every shape runs one warm-up launch and `reps`
  * (>= 1) timed launches on `stream`; the call synchronises the stream.  On
  * success the chosen shape and its mean time per launch (ms) are stored
- * through the pointers that are not NULL.  Errors as for the evaluation
+ * through the pointers that are not NULL.  Where it is one of one or two
+ * states, calls in the other layout (and adjoints with fused source terms) take
+ * the automatic choice.  Errors as for the evaluation
  * calls; PJ_E_INVALID also for a bad mode, reps < 1 or n_states < 1.
  */
 pj_status pj_mech_autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int64_t n_states,
@@ -332,9 +334,9 @@ int64_t pj_mech_lds_bytes(const pj_mech* mech, int for_jacobian);
  * mechanisms hold more states at once.  Per mode, the batch can instead run
  * one launch per segment, each at its mechanism's own launch shape for that
  * mode (pj_batch_set_strategy(batch, mode, 1); 0 = the persistent launch); the
- * graph then holds those launches.  Until one is set, source terms and sparse
- * Jacobians of mechanisms at their automatic launch shapes take whichever is
- * the faster for their sizes, the rest the persistent launch.
+ * graph then holds those launches.  Until one is set, segments of mechanisms
+ * at their automatic launch shapes take whichever is the faster for their
+ * sizes, others the persistent launch.
  *
  * pj_batch_add records a segment (n_states may be 0); adding or clearing
  * segments, or changing the launch shape, discards a captured graph.

@@ -544,8 +544,8 @@ class Batch:
 
     def set_strategy(self, mode: str, per_segment: bool):
         """One persistent launch (False) or one launch per segment at each
-        mechanism's own launch shape (True) for ``mode``; until set, source
-        terms and sparse Jacobians take the faster one for their sizes."""
+        mechanism's own launch shape (True) for ``mode``; until set,
+        mechanisms at their automatic shapes take the faster for their sizes."""
         self._bcheck(_lib.pj_batch_set_strategy(self._h, MODES[mode], int(bool(per_segment))),
                      "pj_batch_set_strategy")
 

@@ -102,9 +102,8 @@ static bool wide_choice(const Mechanism& m, int mode, int64_t n, int& S, int& w)
 //     53 species, 100 states, source terms 57 -> 10, sparse 67 -> 16.5;
 //     111 species, 4096 states, source terms 59 -> 34
 //   more than 256 reactions, Jacobians: 53 species, 71199 states, sparse
-//     1388 -> 1195 (layout F 1375 -> 1338), dense (17799) 408 -> 375; 111 species,
-//     16232 states 752 -> 650 (F 805 -> 764); 360 species, 4096 states 767 -> 682
-//     (F 1270 -> 848)
+//     1388 -> 1110, dense (17799) 408 -> 375; 111 species, 16232 states 752 -> 620
+//     (F 805 -> 716); 360 species, 4096 states 767 -> 660 (F 1270 -> 848)
 //   fewer: 20 species, 131072 states, sparse 996 -> 1159
 static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_t n, int& S, int& w) {
     const int blocks = (m.nr + 63) / 64;
@@ -143,6 +142,10 @@ static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_
     // layout F: two states write twice as long runs; one if two leave a compute
     // unit a single workgroup
     if (layout == PJ_LAYOUT_F) {
+        // (sparse, where eight states fit the scatter kernels: 53 species, 65536
+        // states 1200 us against 1545, whose short runs suffer from a power of two
+        // of states; 300007 states 5786 against 5982)
+        if (mode == MODE_SPARSE && !few && m.f_S[mode] == 8) return false;
         if ((mode == MODE_DENSE || 2 * gather_lds(m.gm, GM_JAC, 2) <= m.lds_max) && take(2, blocks <= 2 * GATHER_BLOCKS ? 4 : 8))
             return true;
     } else if (!few && blocks <= 8 && take(2, 4)) {
@@ -189,6 +192,26 @@ void choose_launch(Mechanism& m) {
         int S = 1;
         for (int c = 4; c >= 1; c >>= 1)
             if (L(c, 1) <= m.lds_max) { S = c; break; }
+        m.auto_S[mode] = S;
+        m.auto_waves[mode] = default_waves(m, mode, S, gr);
+        m.tuned_layout[mode] = -1;
+        // Jacobians in layout F: 8 states write 64 bytes of a value together
+        // (sparse, 4 -> 8 states, us: 13 species, 131072 states 346 -> 275; 20
+        // species 948 -> 894; 53 species, 65536 states 1284 -> 1200, 300007 states
+        // 5964 -> 5786); dense, a state per workgroup: with 8 waves the rows of
+        // 2048 states meet in the same channels (360 species 2759 us, 7 waves
+        // 2635; 2047 states 1851 and 1826)
+        m.f_S[mode] = m.auto_S[mode];
+        m.f_waves[mode] = m.auto_waves[mode];
+        if ((mode == MODE_SPARSE || mode == MODE_DENSE) && !m.dm.det && !m.dm.lsearch) {
+            const int w8 = default_waves(m, mode, 8, gr);
+            if (S == 4 && L(8, w8) <= m.lds_max) {
+                m.f_S[mode] = 8;
+                m.f_waves[mode] = w8;
+            } else if (mode == MODE_DENSE && S == 1 && m.f_waves[mode] == 8) {
+                m.f_waves[mode] = 7;
+            }
+        }
         const int maxS = max_states(kernel_mode(m, mode, false));
         if (m.user_S && m.user_S <= maxS && L(m.user_S, m.user_waves ? m.user_waves : 1) <= m.lds_max)
             S = m.user_S;
@@ -236,16 +259,30 @@ pj_status eval(const pj_mech* mech, int mode, pj_form form, pj_layout layout, in
         return fail(PJ_E_UNSUPPORTED, "per-state working set (" + std::to_string(lds) +
                                           " B) exceeds the LDS of one workgroup");
     int gS = m.S[mode], gw = m.waves[mode];
+    bool automatic = m.automatic[mode];
     const bool fused = mode == pj::MODE_ADJ && dstate;   // J^T v with source terms: scatter kernels
-    if (!fused && (m.automatic[mode] ? pj::gather_choice(m, mode, layout, n, gS, gw)
-                                     : pj::gather_takes(m, mode, layout, n, gS, gw))) {
+    // a shape that was tuned for the gather kernels is no measure for a call that
+    // they don't take, nor for the other layout (111 species, 262144 states, the
+    // shape of layout C in layout F: 18.7 ms, the automatic one 11.9)
+    if (m.tuned_layout[mode] >= 0 &&
+        (m.tuned_layout[mode] != layout || fused || !pj::gather_takes(m, mode, layout, n, gS, gw))) {
+        automatic = true;
+        gS = m.auto_S[mode];
+        gw = m.auto_waves[mode];
+    }
+    int sS = gS, sw = gw;            // the scatter kernels' shape
+    if (automatic && layout == PJ_LAYOUT_F && (n > 2048 || m.f_S[mode] == sS)) {
+        sS = m.f_S[mode];
+        sw = m.f_waves[mode];
+    }
+    if (!fused && (automatic ? pj::gather_choice(m, mode, layout, n, gS, gw) : pj::gather_takes(m, mode, layout, n, gS, gw))) {
         hipError_t e = pj::launch_gather({&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, gS, gw, n, state, param,
                                           dstate, jac, arr, (hipStream_t)stream, vin, grad});
         if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
         g_err.clear();
         return PJ_OK;
     }
-    if (m.automatic[mode] ? pj::wide_choice(m, mode, n, gS, gw) : pj::wide_takes(m, mode, gS, gw)) {
+    if (automatic ? pj::wide_choice(m, mode, n, gS, gw) : pj::wide_takes(m, mode, gS, gw)) {
         hipError_t e = pj::launch_wide({&m.gm, m.d_gm, m.dm.ext, pj::GM_SRC, form, layout, gS, gw, n, state, param, dstate,
                                         nullptr, arr, (hipStream_t)stream, nullptr, nullptr});
         if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
@@ -254,15 +291,16 @@ pj_status eval(const pj_mech* mech, int mode, pj_form form, pj_layout layout, in
     }
     // the hot loop of the static map carries no trace of the run-time search,
     // the fixed-order additions or per-call parameters: kernels of their own
-    const int kmode = kernel_mode(m, mode, arr != nullptr);
-    const int S = std::min(m.S[mode], max_states(kmode));
+    int kmode = kernel_mode(m, mode, arr != nullptr);
+    if (kmode == pj::MODE_DENSE_U16 && sS > 4) kmode = pj::MODE_DENSE;   // built for at most 4 states
+    const int S = std::min(sS, max_states(kmode));
     // a call with its own Arrhenius parameters runs on a copy of the device
     // description that points at them (the mechanism itself is not touched)
     pj::DevMech dm = m.dm;
     dm.arr = pj::gptr(arr);
     hipError_t e = pj::launch(dm, kmode, form, layout, S, n, state, param, dstate, jac, vin, grad,
-                              m.adj_grad_in_lds ? 1 : 0, m.waves[mode], pj::lds_bytes(m.dm, mode, S, m.waves[mode],
-                              m.adj_grad_in_lds), (hipStream_t)stream);
+                              m.adj_grad_in_lds ? 1 : 0, sw, pj::lds_bytes(m.dm, mode, S, sw, m.adj_grad_in_lds),
+                              (hipStream_t)stream);
     if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
     g_err.clear();
     return PJ_OK;
@@ -552,7 +590,8 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
         return fail(PJ_E_DEVICE, "hipEventCreate failed");
     }
     int best_S = m.S[mode], best_w = m.waves[mode];
-    float best = -1.0f;
+    float best = -1.0f, best_scatter = -1.0f;
+    int scatter_S = m.auto_S[mode], scatter_w = m.auto_waves[mode];
     std::string err;
     for (int S = 1; S <= maxS && err.empty(); S *= 2) {
         for (int w = 1; w <= MAX_WAVES * n_du && err.empty(); ++w) {
@@ -587,6 +626,11 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
                 break;
             }
             t /= (float)reps;
+            if (!gather && !wide && (best_scatter < 0.0f || t < best_scatter)) {
+                best_scatter = t;
+                scatter_S = S;
+                scatter_w = wv;
+            }
             if (best < 0.0f || t < best) {
                 best = t;
                 best_S = S;
@@ -599,6 +643,14 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
     (void)hipEventDestroy(e1);
     if (!err.empty()) return fail(PJ_E_DEVICE, err);
     m.automatic[mode] = false;
+    m.tuned_layout[mode] = pj::gather_takes(m, mode, layout, n_states, best_S, best_w) ? layout : -1;
+    if (mode == pj::MODE_ADJ) {
+        // calls with fused source terms stay with the scatter kernels
+        m.auto_S[mode] = scatter_S;
+        m.auto_waves[mode] = scatter_w;
+        m.f_S[mode] = scatter_S;
+        m.f_waves[mode] = scatter_w;
+    }
     m.S[mode] = best_S;
     m.waves[mode] = best_w;
     m.lds[mode] = pj::wide_takes(m, mode, best_S, best_w) ? pj::wide_lds(m.gm, best_w)

@@ -254,17 +254,28 @@ pj_status enqueue_segments(pj_batch* b, int mode, pj_form form, pj_layout layout
 // of 100 states 2679 -> 504; sparse Jacobians of these 2295 -> 1881, 102 -> 57,
 // 2146 -> 1204, of 50 + 5000 + 500 states 152 -> 149; in layout F these last
 // 153 -> 164, of 2000 each 159 -> 167, 3000 + 70000 + 20000 2408 -> 2140, 500
-// each 107 -> 80.  (Adjoint segments may share a parameter-sum buffer, which a
-// launch of its own would clear.)
+// each 107 -> 80; adjoints of 3000 + 70000 + 20000 1705 -> 1301 (not where
+// segments share a parameter-sum buffer, which a launch of its own would clear).
+// Segments of small mechanisms cost less than their launches: 16 of 1024 states
+// of 13 species (one block of 64 reactions), source terms 93 -> 126, sparse
+// Jacobians 224 -> 233.
 bool per_segment(const pj_batch* b, int mode, pj_layout layout) {
     if (b->per_seg[mode] >= 0) return b->per_seg[mode] == 1;
-    if (mode == pj::MODE_ADJ || b->user_S[mode] || b->user_W[mode]) return false;
-    int64_t n = 0;
+    if (b->user_S[mode] || b->user_W[mode]) return false;
+    int64_t n = 0, blocks = 0, k = 0;
     for (auto& sg : b->segs) {
+        if (sg.n == 0) continue;
         if (!sg.mech->m.automatic[mode] || !sg.mech->m.gm.ok || sg.mech->m.dm.det || sg.mech->m.dm.lsearch) return false;
+        if (mode == pj::MODE_ADJ && sg.grad)
+            for (auto& other : b->segs)
+                if (&other != &sg && other.grad == sg.grad) return false;
         n += sg.n;
+        blocks += (sg.mech->m.nr + 63) / 64;
+        ++k;
     }
-    return n > 0 && (mode == pj::MODE_SRC || layout == PJ_LAYOUT_C || n <= 3072 || n >= 32768);
+    if (blocks < 4 * k || n == 0) return false;
+    if (mode == pj::MODE_ADJ) return n >= 32768;
+    return mode == pj::MODE_SRC || layout == PJ_LAYOUT_C || n <= 3072 || n >= 32768;
 }
 
 // the batch as configured for the mode: one persistent launch of shape S x W,

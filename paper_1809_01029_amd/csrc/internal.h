@@ -293,7 +293,10 @@ struct Mechanism {
     size_t off_rec = 0;
     int user_S = 0, user_waves = 0;        // 0 = automatic
     int dense_unroll = 16;                 // dense output: map entries in flight per lane (8 or 16)
-    bool automatic[4] = {}; // the mode's launch shape is the automatic one
+    bool automatic[4] = {};          // the mode's launch shape is the automatic one
+    int tuned_layout[4] = {-1, -1, -1, -1};   // the layout it was tuned in, if the gather kernels won
+    int auto_S[4] = {1, 1, 1, 1}, auto_waves[4] = {1, 1, 1, 1};   // the scatter kernels' automatic shape,
+    int f_S[4] = {1, 1, 1, 1}, f_waves[4] = {1, 1, 1, 1};         // and in layout F (8 states: of more than 2048)
     // gather kernels: tables and the host copy of the reaction records with its
     // byte offset (Arrhenius parameters)
     GatherMech gm{};

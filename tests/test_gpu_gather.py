@@ -93,8 +93,8 @@ def test_automatic_route_agrees(torch_cuda, api, n, op, layout, mech_dir):
     energy of 60 RT is exponentiated) of terms up to the state's largest value: values
     agree to 1e-12 of that."""
     torch = torch_cuda
-    for name in ("ns13", "ns53"):
-        m, path = workload_file(name, mech_dir)
+    for name in ("tiny", "ns13", "ns53"):
+        m, path = tiny_file(3, mech_dir) if name == "tiny" else workload_file(name, mech_dir)
         x, p = synth.pack_state(synth.make_states(m, n, 11), "conp", layout)
         xs, ps = torch.from_numpy(np.ascontiguousarray(x)).cuda(), torch.from_numpy(p.copy()).cuda()
         got = []
