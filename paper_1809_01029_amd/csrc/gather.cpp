@@ -38,23 +38,29 @@ int lanes_of(size_t deg, int len) {
 // cost: the steps of all groups, a group's own cost counted as 8, and the
 // largest share of four waves that take the groups in turn (the others wait for
 // it: 111 species, 262144 states 8.49 ms without that term, 8.35 with it).
-void cut(std::vector<Sum> sums, int bits, bool lp_in_word, uint32_t empty, GatherImage::Lists& out) {
+void cut(const std::vector<Sum>& sums, int bits, bool lp_in_word, uint32_t empty, GatherImage::Lists& out) {
     const int per_word = 32 / bits, head = 3 * per_word, chunk = 4 * per_word;
     int best = -1, full = head + chunk;
+    struct Item {
+        int sum, lanes, len;
+    };
+    std::vector<Item> items(sums.size());
     auto arrange = [&](int f) {
-        auto len = [&](const Sum& s) { return (int)((s.c.size() + lanes_of(s.c.size(), f) - 1) / lanes_of(s.c.size(), f)); };
-        std::stable_sort(sums.begin(), sums.end(), [&](const Sum& a, const Sum& b) {
-            const int pa = lanes_of(a.c.size(), f), pb = lanes_of(b.c.size(), f);
-            return pa != pb ? pa > pb : len(a) > len(b);
+        for (size_t i = 0; i < sums.size(); ++i) {
+            const int p = lanes_of(sums[i].c.size(), f);
+            items[i] = {(int)i, p, (int)((sums[i].c.size() + p - 1) / p)};
+        }
+        std::stable_sort(items.begin(), items.end(), [](const Item& a, const Item& b) {
+            return a.lanes != b.lanes ? a.lanes > b.lanes : a.len > b.len;
         });
-        // first sum, number of sums and steps of each group
+        // first item, number of items and steps of each group
         std::vector<std::array<int, 3>> gr;
-        for (size_t i = 0; i < sums.size();) {
+        for (size_t i = 0; i < items.size();) {
             size_t j = i;
             int used = 0, longest = 0;
-            while (j < sums.size() && used + lanes_of(sums[j].c.size(), f) <= 64) {
-                used += lanes_of(sums[j].c.size(), f);
-                longest = std::max(longest, len(sums[j++]));
+            while (j < items.size() && used + items[j].lanes <= 64) {
+                used += items[j].lanes;
+                longest = std::max(longest, items[j++].len);
             }
             gr.push_back({(int)i, (int)(j - i), longest});
             i = j;
@@ -81,8 +87,8 @@ void cut(std::vector<Sum> sums, int bits, bool lp_in_word, uint32_t empty, Gathe
         out.ext.resize(h0 + 64);
         out.more.resize(out.more.size() + (size_t)(nc - 1) * 64);
         int lane = 0, widest = 0;
-        auto fill = [&](int l, uint32_t meta, int lp, const std::vector<uint32_t>& mine) {
-            std::vector<uint32_t> c = mine;
+        std::vector<uint32_t> c;      // a lane's contributions
+        auto fill = [&](int l, uint32_t meta, int lp) {
             c.resize((size_t)(head + nc * chunk), empty);
             auto word = [&](int k) { return bits == 32 ? c[k] : c[2 * k] | c[2 * k + 1] << 16; };
             uint32_t w0 = word(0);
@@ -92,22 +98,23 @@ void cut(std::vector<Sum> sums, int bits, bool lp_in_word, uint32_t empty, Gathe
             for (int x = 0; x < nc; ++x)
                 (x ? out.more[(more0 + x - 1) * 64 + l] : out.ext[h0 + l]) =
                     make_uint4(word(3 + 4 * x), word(4 + 4 * x), word(5 + 4 * x), word(6 + 4 * x));
+            c.clear();
         };
         for (int k = q[0]; k < q[0] + q[1]; ++k) {
-            const int P = lanes_of(sums[k].c.size(), full);
+            const Sum& sum = sums[items[k].sum];
+            const int P = items[k].lanes;
             int lp = 0;
             while ((1 << lp) < P) ++lp;
             widest = std::max(widest, lp);
             // contribution j to lane j mod P: neighbouring lanes then read
             // neighbouring reactions of a sum that many contribute to
             for (int l = 0; l < P; ++l) {
-                std::vector<uint32_t> mine;
-                for (size_t j = l; j < sums[k].c.size(); j += P) mine.push_back(sums[k].c[j]);
-                fill(lane + l, l ? 0xFFFFFFFFu : sums[k].meta, lp, mine);
+                for (size_t j = l; j < sum.c.size(); j += P) c.push_back(sum.c[j]);
+                fill(lane + l, l ? 0xFFFFFFFFu : sum.meta, lp);
             }
             lane += P;
         }
-        for (; lane < 64; ++lane) fill(lane, 0xFFFFFFFFu, 0, {});
+        for (; lane < 64; ++lane) fill(lane, 0xFFFFFFFFu, 0);
         out.desc.push_back(make_uint2((uint32_t)widest | (uint32_t)(nc - 1) << 8, (uint32_t)more0));
     }
 }
@@ -343,7 +350,7 @@ void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std:
         for (int i = R.row0; i < R.row1; ++i)
             for (int e = m.row_ptr[i] + 2; e < m.row_ptr[i + 1]; ++e) {
                 Sum s{(uint32_t)(e - R.e0) | (uint32_t)(m.col_idx[e] - 2) << 16 |
-                          (uint32_t)(i - 2 < ns ? dense_of[i - 2] + 1 : 0) << gm.dshift, ent[e]};
+                          (uint32_t)(i - 2 < ns ? dense_of[i - 2] + 1 : 0) << gm.dshift, std::move(ent[e])};
                 (s.c.size() > 6 ? heavy : s.c.size() > 2 ? mid : light).push_back(std::move(s));
             }
         auto longer = [](const Sum& a, const Sum& b) { return a.c.size() > b.c.size(); };

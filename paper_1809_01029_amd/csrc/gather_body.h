@@ -1448,16 +1448,10 @@ hipError_t launch_gather_impl(const GatherCall& c) {
     if (c.form == F && c.layout == L && c.gmode == M && c.S == SS) return launch_gather_t<F, L, M, SS, EXT>(c);
 #define PJ_GA(F, L) \
     if (c.form == F && c.layout == L && c.gmode == GM_ADJ && c.S == 1) return launch_gather_adjoint_t<F, L, EXT>(c);
-#ifdef PJ_QUICK
-    PJ_GA(PJ_CONP, PJ_LAYOUT_C)
-#define PJ_GS(F, L, M) PJ_G(F, L, M, 1) PJ_G(F, L, M, 2)
-    PJ_GS(PJ_CONP, PJ_LAYOUT_C, GM_SRC) PJ_GS(PJ_CONP, PJ_LAYOUT_C, GM_JAC)
-#else
 #define PJ_GS(F, L, M) PJ_G(F, L, M, 1) PJ_G(F, L, M, 2)
 #define PJ_GL(F, L) PJ_GS(F, L, GM_SRC) PJ_GS(F, L, GM_JAC) PJ_GS(F, L, GM_DENSE) PJ_GA(F, L)
     PJ_GL(PJ_CONP, PJ_LAYOUT_C) PJ_GL(PJ_CONP, PJ_LAYOUT_F) PJ_GL(PJ_CONV, PJ_LAYOUT_C) PJ_GL(PJ_CONV, PJ_LAYOUT_F)
 #undef PJ_GL
-#endif
 #undef PJ_GS
 #undef PJ_G
 #undef PJ_GA

@@ -185,9 +185,9 @@ static_assert(sizeof(FastRec) == 64 && sizeof(FastEff) == 96, "record sizes");
 // bits of FastRec::info: kind 0..2, reversible 3, depends on the bath gas 4,
 // chemically activated 5, dnu + 3 in 8..10, molecules of each side in 12..13
 // and 14..15, slots that hold the bath gas in 16..21, third bodies in 24..27
-// (FastRec::chunk) a reaction of the chunk depends on the pressure or a third body
-constexpr uint32_t CHUNK_PRESSURE = 1u << 15;
 constexpr uint32_t GI_REV = 1u << 3, GI_BATH = 1u << 4, GI_CHEMACT = 1u << 5;
+// bit of FastRec::chunk: a reaction of the chunk depends on the pressure or a third body
+constexpr uint32_t CHUNK_PRESSURE = 1u << 15;
 
 // A set of sums whose lists are cut into groups of 64 lanes.  Every lane has
 // three words of contributions in its head and four in its ext, both found

@@ -36,7 +36,8 @@ constexpr int WIDE_STATES = 64;
 
 enum { F_C = 0, F_E = 1, F_I = 2, F_W = 3, WIDE_ROWS = 4 };
 constexpr int WIDE_THREADS = 1024;
-enum { WS_T = 0, WS_V, WS_P, WS_CB, WS_N };
+// (at the end T's row holds dT/dt)
+enum { WS_T = 0, WS_V, WS_P, WS_SDOT, WS_N };
 
 // LDS of a workgroup in doubles: species records (one double longer than their
 // rows: reads and writes along the species meet different banks; two for each
@@ -200,7 +201,7 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
     const PJ_GLOBAL uint32_t* const falls = (const PJ_GLOBAL uint32_t*)gm->fall;
     const int l16 = lane >> 4, w16 = lane & 15;
     // a batch: reactions wave + nwave (4 b + 0..3), so that every wave has its
-    // share of each class; past the end, reaction nr_pad - 1 of no kind and no slots
+    // share of each class; past the end, a record of no kind and empty slots
     auto reaction = [&](int b) {
         const int p = wave + nwave * (4 * b + l16);
         return p < nr ? p : -1;
@@ -389,20 +390,20 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
         }
         const double Tdot = -T * np / Dp;
         sc[WS_T * S + s] = Tdot;
-        sc[WS_CB * S + s] = FORM == PJ_CONP ? Vv * Tdot * invT + Vv * RU * T * om / P : P * Tdot * invT + RU * T * om;
+        sc[WS_SDOT * S + s] = FORM == PJ_CONP ? Vv * Tdot * invT + Vv * RU * T * om / P : P * Tdot * invT + RU * T * om;
     }
     __syncthreads();
     if (LAYOUT == PJ_LAYOUT_F) {
         if (st < n)
             for (int i = g; i < N; i += G)
-                dstate[(long)i * n + st] = i == 0 ? sc[WS_T * S + s] : i == 1 ? sc[WS_CB * S + s] : Vv * at_(i - 2, F_W);
+                dstate[(long)i * n + st] = i == 0 ? sc[WS_T * S + s] : i == 1 ? sc[WS_SDOT * S + s] : Vv * at_(i - 2, F_W);
     } else {
         double* const out = dstate + qg * (S * (long)N);
         const int total = (int)((n - qg * S < S ? n - qg * S : S)) * N;
 #pragma unroll 4
         for (int e = tid; e < total; e += nthr) {
             const int q = by_N(e), i = e - q * N;
-            out[e] = i == 0 ? sc[WS_T * S + q] : i == 1 ? sc[WS_CB * S + q] : sc[WS_V * S + q] * sp[(i - 2) * REC + F_W * S + q];
+            out[e] = i == 0 ? sc[WS_T * S + q] : i == 1 ? sc[WS_SDOT * S + q] : sc[WS_V * S + q] * sp[(i - 2) * REC + F_W * S + q];
         }
     }
 }
