@@ -284,7 +284,10 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
         const V2 kf = vmap(lnkf, [](double x) { return fexp_in(x); });
         const V2 Pf = both([](const Rxn& r) { return r.c[0] * r.c[1] * r.c[2]; });
         const V2 Pb = both([](const Rxn& r) { return r.w & GI_REV ? r.c[3] * r.c[4] * r.c[5] : 0.0; });
-        const V2 kq = both([](const Rxn& r) { return ((r.x[0] * r.x[3]) * (r.x[1] * r.x[4]) * (r.x[2] * r.x[5])) * r.pw; });
+        // (an irreversible reaction's is 0: its product may overflow with k_f, and inf * 0 is NaN)
+        const V2 kq = both([](const Rxn& r) {
+            return r.w & GI_REV ? ((r.x[0] * r.x[3]) * (r.x[1] * r.x[4]) * (r.x[2] * r.x[5])) * r.pw : 0.0;
+        });
         q = kf * Pf - (kf * kq) * Pb;
     };
     auto rate = [&](const Rxn& r, uint32_t rec, const Extra& ex, int l, double lnkf, double q) {
