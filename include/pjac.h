@@ -270,6 +270,17 @@ int pj_mech_waves_per_state(const pj_mech* mech, int for_jacobian);
  * 3 (adjoint, at most 4 states per workgroup), of a large call in layout C
  * where the choice is automatic; -1 on error */
 int pj_mech_launch_shape(const pj_mech* mech, int mode, int* states_per_group, int* waves_per_group);
+/*
+ * What a call of n_states (>= 1) in `layout` runs at the mechanism's present
+ * launch shape: 0 the scatter kernels (LDS additions), 1 the gather kernels
+ * (one or two states per workgroup, fixed order), 2 the wide kernel (source
+ * terms, a lane per state; *waves_per_group counts pairs of waves), and its
+ * shape through the pointers that are not NULL.  fused: non-zero for an
+ * adjoint with source terms.  -1 for a NULL or not uploaded mechanism, a bad
+ * mode, layout or n_states.
+ */
+int pj_mech_kernel(const pj_mech* mech, int mode, pj_layout layout, int64_t n_states, int fused, int* states_per_group,
+                   int* waves_per_group);
 
 /*
  * The dense Jacobian's output loop reads the (row, column) -> CSR slot map of
@@ -349,7 +360,9 @@ int64_t pj_mech_lds_bytes(const pj_mech* mech, int for_jacobian);
  * fastest for that mode: *states_per_group and *waves_per_group receive 0
  * when the per-segment launches win (the best persistent shape is kept as
  * the mode's launch shape either way).  pj_batch_strategy returns the mode's
- * strategy as set (0 or 1; 0 while none is; -1 for a NULL batch or a bad mode).  Errors as for the
+ * strategy as set (0 or 1; 0 while none is; -1 for a NULL batch or a bad mode),
+ * pj_batch_route what an evaluation in `layout` runs: 0 the persistent launch,
+ * 1 a launch per segment (-1 also for a bad layout).  Errors as for the
  * per-mechanism calls, with the segment index in the message
  * (pj_batch_last_error).
  */
@@ -366,6 +379,7 @@ int pj_batch_launch_shape(const pj_batch* batch, int mode, int* states_per_group
 int pj_batch_segment_states(const pj_batch* batch, int mode, int segment);
 pj_status pj_batch_set_strategy(pj_batch* batch, int mode, int per_segment);
 int pj_batch_strategy(const pj_batch* batch, int mode);
+int pj_batch_route(const pj_batch* batch, int mode, pj_layout layout);
 pj_status pj_batch_eval(pj_batch* batch, int mode, pj_form form, pj_layout layout, pj_stream stream);
 pj_status pj_batch_eval_graph(pj_batch* batch, int mode, pj_form form, pj_layout layout, pj_stream stream);
 /*

@@ -109,6 +109,8 @@ _lib.pj_batch_set_strategy.argtypes = [_P, ctypes.c_int, ctypes.c_int]
 _lib.pj_batch_set_strategy.restype = ctypes.c_int
 _lib.pj_batch_strategy.argtypes = [_P, ctypes.c_int]
 _lib.pj_batch_strategy.restype = ctypes.c_int
+_lib.pj_batch_route.argtypes = [_P, ctypes.c_int, ctypes.c_int]
+_lib.pj_batch_route.restype = ctypes.c_int
 _lib.pj_batch_last_error.argtypes = []
 _lib.pj_batch_last_error.restype = ctypes.c_char_p
 _lib.pj_mech_set_waves_per_state.argtypes = [_P, ctypes.c_int]
@@ -119,6 +121,9 @@ _lib.pj_mech_set_launch.argtypes = [_P, ctypes.c_int, ctypes.c_int]
 _lib.pj_mech_set_launch.restype = ctypes.c_int
 _lib.pj_mech_launch_shape.argtypes = [_P, ctypes.c_int, ctypes.POINTER(ctypes.c_int), ctypes.POINTER(ctypes.c_int)]
 _lib.pj_mech_launch_shape.restype = ctypes.c_int
+_lib.pj_mech_kernel.argtypes = [_P, ctypes.c_int, ctypes.c_int, _I64, ctypes.c_int, ctypes.POINTER(ctypes.c_int),
+                                ctypes.POINTER(ctypes.c_int)]
+_lib.pj_mech_kernel.restype = ctypes.c_int
 _lib.pj_mech_set_dense_unroll.argtypes = [_P, ctypes.c_int]
 _lib.pj_mech_set_dense_unroll.restype = ctypes.c_int
 _lib.pj_mech_dense_unroll.argtypes = [_P]
@@ -228,6 +233,17 @@ class Mechanism:
         if _lib.pj_mech_launch_shape(self._h, int(mode), ctypes.byref(a), ctypes.byref(b)) != 0:
             raise PjError(1, "pj_mech_launch_shape")
         return a.value, b.value
+
+    def kernel(self, mode: str, layout: str, n_states: int, fused: bool = False):
+        """(kernel set, states per workgroup, waves) that a call of ``n_states``
+        runs (pj_mech_kernel): "scatter", "gather" or "wide" (waves in pairs).
+        ``fused``: an adjoint with source terms."""
+        a, b = ctypes.c_int(), ctypes.c_int()
+        k = _lib.pj_mech_kernel(self._h, MODES[mode], LAYOUTS[layout], int(n_states), int(bool(fused)), ctypes.byref(a),
+                                ctypes.byref(b))
+        if k < 0:
+            raise PjError(1, "pj_mech_kernel")
+        return ("scatter", "gather", "wide")[k], a.value, b.value
 
     def arrhenius(self):
         """(ln A, b, Ea/R) of every reaction, description order (k_inf for falloff)."""
@@ -551,6 +567,10 @@ class Batch:
 
     def strategy(self, mode: str) -> bool:
         return _lib.pj_batch_strategy(self._h, MODES[mode]) == 1
+
+    def route(self, mode: str, layout: str = "F") -> str:
+        """What an evaluation runs: "persistent" or "per_segment" (pj_batch_route)."""
+        return ("persistent", "per_segment")[_lib.pj_batch_route(self._h, MODES[mode], LAYOUTS[layout])]
 
     def eval(self, mode: str, form: str = "conp", layout: str = "F", graph: bool = False, stream=None):
         f = _lib.pj_batch_eval_graph if graph else _lib.pj_batch_eval

@@ -166,6 +166,30 @@ static void nominal_shape(const Mechanism& m, int mode, int& S, int& w, int64_t&
         lds = wide_lds(m.gm, w);
 }
 
+// the kernel set of a call of n states and its launch shape
+Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fused) {
+    int S = m.S[mode], w = m.waves[mode];
+    bool automatic = m.automatic[mode];
+    // a shape that was tuned for the gather kernels is no measure for a call that
+    // they don't take, nor for the other layout (111 species, 262144 states, the
+    // shape of layout C in layout F: 18.7 ms, the automatic one 13.1)
+    if (m.tuned_layout[mode] >= 0 && (m.tuned_layout[mode] != layout || fused || !gather_takes(m, mode, layout, n, S, w))) {
+        automatic = true;
+        S = m.auto_S[mode];
+        w = m.auto_waves[mode];
+    }
+    int sS = S, sw = w;              // the scatter kernels' shape
+    if (automatic && layout == PJ_LAYOUT_F && (n > 2048 || m.f_S[mode] == sS)) {
+        sS = m.f_S[mode];
+        sw = m.f_waves[mode];
+    }
+    // (the adjoint with fused source terms: scatter kernels)
+    if (!fused && (automatic ? gather_choice(m, mode, layout, n, S, w) : gather_takes(m, mode, layout, n, S, w)))
+        return {KERNEL_GATHER, S, w};
+    if (automatic ? wide_choice(m, mode, n, S, w) : wide_takes(m, mode, S, w)) return {KERNEL_WIDE, S, w};
+    return {KERNEL_SCATTER, sS, sw};
+}
+
 // Waves per workgroup for S states per workgroup: enough that a compute unit
 // holds about 8 resident waves given how many workgroups fit in its LDS, and
 // at least S/64 so that every state has a lane.
@@ -258,33 +282,11 @@ pj_status eval(const pj_mech* mech, int mode, pj_form form, pj_layout layout, in
     if (lds > m.lds_max)
         return fail(PJ_E_UNSUPPORTED, "per-state working set (" + std::to_string(lds) +
                                           " B) exceeds the LDS of one workgroup");
-    int gS = m.S[mode], gw = m.waves[mode];
-    bool automatic = m.automatic[mode];
-    const bool fused = mode == pj::MODE_ADJ && dstate;   // J^T v with source terms: scatter kernels
-    // a shape that was tuned for the gather kernels is no measure for a call that
-    // they don't take, nor for the other layout (111 species, 262144 states, the
-    // shape of layout C in layout F: 18.7 ms, the automatic one 13.1)
-    if (m.tuned_layout[mode] >= 0 &&
-        (m.tuned_layout[mode] != layout || fused || !pj::gather_takes(m, mode, layout, n, gS, gw))) {
-        automatic = true;
-        gS = m.auto_S[mode];
-        gw = m.auto_waves[mode];
-    }
-    int sS = gS, sw = gw;            // the scatter kernels' shape
-    if (automatic && layout == PJ_LAYOUT_F && (n > 2048 || m.f_S[mode] == sS)) {
-        sS = m.f_S[mode];
-        sw = m.f_waves[mode];
-    }
-    if (!fused && (automatic ? pj::gather_choice(m, mode, layout, n, gS, gw) : pj::gather_takes(m, mode, layout, n, gS, gw))) {
-        hipError_t e = pj::launch_gather({&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, gS, gw, n, state, param,
-                                          dstate, jac, arr, (hipStream_t)stream, vin, grad});
-        if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
-        g_err.clear();
-        return PJ_OK;
-    }
-    if (automatic ? pj::wide_choice(m, mode, n, gS, gw) : pj::wide_takes(m, mode, gS, gw)) {
-        hipError_t e = pj::launch_wide({&m.gm, m.d_gm, m.dm.ext, pj::GM_SRC, form, layout, gS, gw, n, state, param, dstate,
-                                        nullptr, arr, (hipStream_t)stream, nullptr, nullptr});
+    const pj::Route r = pj::route(m, mode, layout, n, mode == pj::MODE_ADJ && dstate);
+    if (r.kernel != pj::KERNEL_SCATTER) {
+        const pj::GatherCall c{&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, r.S, r.waves, n, state, param,
+                               dstate, jac, arr, (hipStream_t)stream, vin, grad};
+        hipError_t e = r.kernel == pj::KERNEL_GATHER ? pj::launch_gather(c) : pj::launch_wide(c);
         if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
         g_err.clear();
         return PJ_OK;
@@ -292,14 +294,14 @@ pj_status eval(const pj_mech* mech, int mode, pj_form form, pj_layout layout, in
     // the hot loop of the static map carries no trace of the run-time search,
     // the fixed-order additions or per-call parameters: kernels of their own
     int kmode = kernel_mode(m, mode, arr != nullptr);
-    if (kmode == pj::MODE_DENSE_U16 && sS > 4) kmode = pj::MODE_DENSE;   // built for at most 4 states
-    const int S = std::min(sS, max_states(kmode));
+    if (kmode == pj::MODE_DENSE_U16 && r.S > 4) kmode = pj::MODE_DENSE;   // built for at most 4 states
+    const int S = std::min(r.S, max_states(kmode));
     // a call with its own Arrhenius parameters runs on a copy of the device
     // description that points at them (the mechanism itself is not touched)
     pj::DevMech dm = m.dm;
     dm.arr = pj::gptr(arr);
     hipError_t e = pj::launch(dm, kmode, form, layout, S, n, state, param, dstate, jac, vin, grad,
-                              m.adj_grad_in_lds ? 1 : 0, sw, pj::lds_bytes(m.dm, mode, S, sw, m.adj_grad_in_lds),
+                              m.adj_grad_in_lds ? 1 : 0, r.waves, pj::lds_bytes(m.dm, mode, S, r.waves, m.adj_grad_in_lds),
                               (hipStream_t)stream);
     if (e != hipSuccess) return fail(PJ_E_DEVICE, std::string("kernel launch failed: ") + hipGetErrorString(e));
     g_err.clear();
@@ -539,6 +541,19 @@ int pj_mech_waves_per_state(const pj_mech* mech, int for_jacobian) {
     int64_t lds;
     pj::nominal_shape(mech->m, mode, S, w, lds);
     return S == 1 ? w : -1;
+}
+
+int pj_mech_kernel(const pj_mech* mech, int mode, pj_layout layout, int64_t n_states, int fused, int* states_per_group,
+                   int* waves_per_group) {
+    if (!mech || !mech->m.dbuf || mode < 0 || mode >= pj::N_MODES || n_states < 1 ||
+        (layout != PJ_LAYOUT_F && layout != PJ_LAYOUT_C))
+        return -1;
+    const pj::Mechanism& m = mech->m;
+    const pj::Route r = pj::route(m, mode, layout, n_states, mode == pj::MODE_ADJ && fused);
+    if (states_per_group)
+        *states_per_group = r.kernel == pj::KERNEL_SCATTER ? std::min(r.S, max_states(kernel_mode(m, mode, false))) : r.S;
+    if (waves_per_group) *waves_per_group = r.waves;
+    return r.kernel;
 }
 
 pj_status pj_mech_set_dense_unroll(pj_mech* mech, int entries) {

@@ -396,6 +396,11 @@ int pj_batch_strategy(const pj_batch* b, int mode) {
     return b->per_seg[mode] == 1;
 }
 
+int pj_batch_route(const pj_batch* b, int mode, pj_layout layout) {
+    if (!b || !batch_mode(mode) || (layout != PJ_LAYOUT_F && layout != PJ_LAYOUT_C)) return -1;
+    return per_segment(b, mode, layout);
+}
+
 pj_status pj_batch_eval(pj_batch* b, int mode, pj_form form, pj_layout layout, pj_stream stream) {
     if (!b) return fail(PJ_E_INVALID, "NULL batch");
     pj_status r = check_segments(b, mode, form, layout);

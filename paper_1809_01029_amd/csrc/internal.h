@@ -373,6 +373,14 @@ int64_t wide_lds(const GatherMech& gm, int waves);
 hipError_t launch_wide(const GatherCall& c);
 hipError_t launch_wide_ext(const GatherCall& c);
 
+// api.cpp: the kernel set that evaluates a call, and its launch shape (KERNEL_WIDE:
+// pairs of waves); fused: an adjoint with source terms
+enum Kernel : int { KERNEL_SCATTER = 0, KERNEL_GATHER = 1, KERNEL_WIDE = 2 };
+struct Route {
+    int kernel, S, waves;
+};
+Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fused);
+
 // kernels.hip (kernel_body.h)
 enum Mode : int { MODE_SRC = 0, MODE_SPARSE = 1, MODE_DENSE = 2, MODE_ADJ = 3,
                   MODE_SPARSE_LS = 4 /* sparse with run-time slot search; launch shape of MODE_SPARSE */,

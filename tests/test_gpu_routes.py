@@ -1,0 +1,132 @@
+"""Which kernels a call runs, on both sides of every line of the automatic
+choice, and the results of both: the route is asserted, so that a case cannot
+slip to the other side of its line, and sampled states (the first, the last and
+some between) are compared with the oracle under ``oracle.gates``."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle.gates import check_jac, check_source
+from paper_1809_01029_amd import synth
+from conftest import workload_file
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def torch_cuda():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    return torch
+
+
+@pytest.fixture(scope="module")
+def api(torch_cuda):
+    from paper_1809_01029_amd import api as a
+    return a
+
+
+def sample(n, k=6):
+    return np.unique(np.concatenate([[0, n - 1], np.linspace(0, n - 1, k).astype(int)]))
+
+
+class Segment:
+    def __init__(self, torch, api, mech_dir, name, n, mode, layout, seed, dstate=False, grad=None):
+        self.m, self.path = workload_file(name, mech_dir)
+        self.x, self.p = synth.pack_state(synth.make_states(self.m, n, seed), "conp", "C")
+        self.layout, self.n = layout, n
+        self.mech = api.load_mechanism(self.path)
+        dev = lambda a: torch.from_numpy(np.ascontiguousarray(a if layout == "C" else a.T)).cuda()  # noqa: E731
+        self.xs, self.ps = dev(self.x), torch.from_numpy(self.p.copy()).cuda()
+        self.kw = {}
+        if mode == "sparse":
+            self.kw["out"] = torch.zeros((n, self.mech.nnz) if layout == "C" else (self.mech.nnz, n), dtype=torch.float64,
+                                         device="cuda")
+        if mode == "adjoint":
+            self.v = np.random.default_rng(seed).standard_normal(self.x.shape)
+            self.kw.update(out=torch.zeros_like(self.xs), v=dev(self.v),
+                           grad=torch.full((3, self.m.n_reactions), 7.0, dtype=torch.float64, device="cuda")
+                           if grad is None else grad)
+        if mode != "adjoint" or dstate:
+            self.kw["dstate"] = torch.zeros_like(self.xs)
+
+    def states_of(self, t, idx):
+        return (t[idx] if self.layout == "C" else t[:, idx].t()).cpu().numpy()
+
+    def check(self, torch, api, mode, what):
+        if not self.n:
+            return
+        idx = sample(self.n)
+        ti = torch.from_numpy(idx).cuda()
+        o = oracle.Oracle(self.path)
+        x, p = self.x[idx], self.p[idx]
+        if "dstate" in self.kw:
+            f_o, f_b = o.source(x, p, "conp", bound=True)
+            check_source(self.states_of(self.kw["dstate"], ti), f_o, f_b, what + " source terms")
+        if mode == "sparse":
+            J_o, J_b = o.jacobian(x, p, "conp", bound=True)
+            check_jac(api.sparse_to_dense(self.mech, self.states_of(self.kw["out"], ti), "C"), J_o, J_b, what + " Jacobian")
+        if mode == "adjoint":
+            j_o, _, j_b, _ = o.adjoint(x, p, self.v[idx], "conp", bound=True)
+            check_jac(self.states_of(self.kw["out"], ti), j_o, j_b, what + " J^T v")
+
+
+# (13, 53 and 111 species: 1, 6 and 13 blocks of 64 reactions; four a segment
+# or more on average let the automatic choice launch per segment)
+@pytest.mark.parametrize("graph", [False, True])
+@pytest.mark.parametrize("mode,layout,sizes,fused,want", [
+    ("source", "C", (1, 0, 3), False, "per_segment"),
+    ("source", "F", (1025, 9000, 130), False, "per_segment"),
+    ("sparse", "C", (700, 3000, 500), False, "per_segment"),
+    ("sparse", "F", (1000, 1572, 500), False, "per_segment"),
+    ("sparse", "F", (1000, 1573, 500), False, "persistent"),
+    ("sparse", "F", (30000, 2067, 700), False, "persistent"),
+    ("sparse", "F", (30000, 2068, 700), False, "per_segment"),
+    ("adjoint", "C", (30000, 2000, 767), False, "persistent"),
+    ("adjoint", "C", (30000, 2000, 768), False, "per_segment"),
+    ("adjoint", "F", (0, 30001, 3001), False, "per_segment"),
+    ("adjoint", "C", (1, 2, 3), True, "persistent"),
+])
+def test_batch_automatic_route(torch_cuda, api, mode, layout, sizes, fused, want, graph, mech_dir):
+    torch = torch_cuda
+    b = api.Batch()
+    segs = [Segment(torch, api, mech_dir, name, n, mode, layout, 2 + k, dstate=fused)
+            for k, (name, n) in enumerate(zip(("ns13", "ns53", "ns111"), sizes))]
+    for sg in segs:
+        b.add(sg.mech, sg.xs, sg.ps, layout, **sg.kw)
+    assert b.route(mode, layout) == want and not b.strategy(mode)
+    for again in range(2):
+        b.eval(mode, "conp", layout, graph=graph)
+        torch.cuda.synchronize()
+        for k, sg in enumerate(segs):
+            sg.check(torch, api, mode, f"{mode} {layout} {sizes} graph={graph} run {again} segment {k}")
+    if mode == "adjoint":
+        # the parameter sums of the persistent launch: sums of n terms in another order
+        sums = [sg.kw["grad"].clone() for sg in segs]
+        b.set_strategy(mode, False)
+        assert b.route(mode, layout) == "persistent"
+        b.eval(mode, "conp", layout)
+        torch.cuda.synchronize()
+        for g, sg in zip(sums, segs):
+            scale = sg.kw["grad"].abs().amax(dim=1, keepdim=True)
+            assert bool(((g - sg.kw["grad"]).abs() <= 1e-11 * scale).all())
+
+
+def test_batch_segments_that_share_their_parameter_sums(torch_cuda, api, mech_dir):
+    """Two segments with one buffer: the sums of both, which a launch of its own
+    would clear."""
+    torch = torch_cuda
+    one = Segment(torch, api, mech_dir, "ns111", 20000, "adjoint", "C", 5)
+    two = Segment(torch, api, mech_dir, "ns111", 20000, "adjoint", "C", 6, grad=one.kw["grad"])
+    b = api.Batch()
+    for sg in (one, two):
+        b.add(sg.mech, sg.xs, sg.ps, "C", **sg.kw)
+    assert b.route("adjoint", "C") == "persistent"
+    b.eval("adjoint", "conp", "C")
+    want = sum(api.eval_adjoint(sg.mech, sg.xs, sg.ps, sg.kw["v"], "conp", "C")[1] for sg in (one, two))
+    torch.cuda.synchronize()
+    scale = want.abs().amax(dim=1, keepdim=True)
+    assert bool(((one.kw["grad"] - want).abs() <= 1e-11 * scale).all())
+    for sg in (one, two):
+        sg.check(torch, api, "adjoint", "shared sums")
