@@ -255,7 +255,9 @@ pj_status enqueue_segments(pj_batch* b, int mode, pj_form form, pj_layout layout
 // 2146 -> 1204, of 50 + 5000 + 500 states 152 -> 149; in layout F these last
 // 153 -> 164, of 2000 each 159 -> 167, 3000 + 70000 + 20000 2408 -> 2140, 500
 // each 107 -> 80; adjoints of 3000 + 70000 + 20000 1705 -> 1301 (not where
-// segments share a parameter-sum buffer, which a launch of its own would clear).
+// segments share a parameter-sum buffer, which a launch of its own would clear;
+// nor with fused source terms, which the scatter kernels evaluate either way:
+// 1704 -> 1851, layout F 1703 -> 1874).
 // Segments of small mechanisms cost less than their launches: 16 of 1024 states
 // of 13 species (one block of 64 reactions), source terms 93 -> 126, sparse
 // Jacobians 224 -> 233.
@@ -266,6 +268,7 @@ bool per_segment(const pj_batch* b, int mode, pj_layout layout) {
     for (auto& sg : b->segs) {
         if (sg.n == 0) continue;
         if (!sg.mech->m.automatic[mode] || !sg.mech->m.gm.ok || sg.mech->m.dm.det || sg.mech->m.dm.lsearch) return false;
+        if (mode == pj::MODE_ADJ && sg.dstate) return false;
         if (mode == pj::MODE_ADJ && sg.grad)
             for (auto& other : b->segs)
                 if (&other != &sg && other.grad == sg.grad) return false;

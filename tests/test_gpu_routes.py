@@ -87,6 +87,9 @@ class Segment:
     ("adjoint", "C", (30000, 2000, 768), False, "per_segment"),
     ("adjoint", "F", (0, 30001, 3001), False, "per_segment"),
     ("adjoint", "C", (1, 2, 3), True, "persistent"),
+    # (with source terms every segment's kernels are the persistent launch's)
+    ("adjoint", "C", (3000, 30000, 2000), True, "persistent"),
+    ("adjoint", "F", (3000, 30000, 2000), True, "persistent"),
 ])
 def test_batch_automatic_route(torch_cuda, api, mode, layout, sizes, fused, want, graph, mech_dir):
     torch = torch_cuda
