@@ -254,10 +254,10 @@ pj_status pj_mech_get_arrhenius(const pj_mech* mech, double* lnA, double* b, dou
  * one state (without fused source terms); its parameter sums are added over
  * the workgroups in any order.
  * Source terms of 64 states with at least 2 waves run a lane per state where
- * four rows of the species fit the LDS (about 75 species); there
- * waves_per_group counts pairs of waves.
+ * two rows of the species fit the LDS (about 110 species), also in a fixed
+ * order; there waves_per_group counts pairs of waves.
  * With one wave per workgroup every accumulation happens in a fixed order
- * too, so results are bitwise reproducible; with more (and 4 or more states),
+ * too, so results are bitwise reproducible; with more (and 4 to 32 states),
  * the order of LDS atomic additions across waves may vary between runs
  * (results then agree to rounding).  pj_mech_set_waves_per_state(w) is pj_mech_set_launch(1, w)
  * (w in 1, 2, 4; 0 = automatic).

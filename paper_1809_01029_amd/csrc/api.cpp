@@ -69,7 +69,7 @@ static bool gather_takes(const Mechanism& m, int mode, pj_layout layout, int64_t
 // Source terms of 64 states per workgroup and at least 2 waves (pairs of them)
 // run on the wide kernel (wide_body.h).
 static bool wide_takes(const Mechanism& m, int mode, int S, int w) {
-    return mode == MODE_SRC && m.gm.ok && !m.dm.det && S == 64 && w >= 2 && wide_lds(m.gm, w) <= m.lds_max;
+    return mode == MODE_SRC && m.gm.ok && !m.dm.det && S == 64 && w >= 2 && wide_fits(m.gm, w);
 }
 
 // The automatic choice of the wide kernel.  Measured on MI355X, scatter (4

@@ -119,6 +119,66 @@ void cut(const std::vector<Sum>& sums, int bits, bool lp_in_word, uint32_t empty
     }
 }
 
+// The wide kernel's sums for 2 w waves.  All wait for the wave with the most words,
+// so a list longer than a wave's share is dealt to parts (further parts go to rows
+// of species, at most one for each but the bath gas), and the parts, the longest
+// first, to the wave with the fewest words.
+void deal(const std::vector<Sum>& sp, int w, GatherImage& g) {
+    const int ns = (int)sp.size(), waves = 2 * w;
+    size_t total = 0;
+    for (auto& s : sp) total += s.c.size();
+    size_t len = std::max<size_t>(1, (total + waves - 1) / waves);
+    auto parts = [&](const Sum& s) { return std::max<size_t>(1, (s.c.size() + len - 1) / len); };
+    for (;; ++len) {
+        size_t more = 0;
+        for (auto& s : sp) more += parts(s) - 1;
+        if ((int)more < ns) break;
+    }
+    struct Part {
+        int to;
+        std::vector<uint32_t> c;
+    };
+    std::vector<Part> all;
+    std::vector<int32_t> xs{0};
+    for (auto& s : sp) {
+        const size_t n = parts(s);
+        for (size_t q = 0; q < n; ++q) {
+            Part t{q ? ns + xs.back() + (int)q - 1 : (int)s.meta, {}};
+            for (size_t j = q; j < s.c.size(); j += n) t.c.push_back(s.c[j]);
+            all.push_back(std::move(t));
+        }
+        xs.push_back(xs.back() + (int)n - 1);
+    }
+    std::stable_sort(all.begin(), all.end(), [](const Part& a, const Part& b) { return a.c.size() > b.c.size(); });
+    std::vector<std::vector<const Part*>> of(waves);
+    std::vector<size_t> load(waves, 0);
+    for (auto& t : all) {
+        int best = -1;
+        for (int v = 0; v < waves; ++v)
+            if ((int)of[v].size() < WIDE_OWN && (best < 0 || load[v] < load[best])) best = v;
+        if (best < 0) return;      // more than the waves hold
+        of[best].push_back(&t);
+        load[best] += t.c.size();
+    }
+    g.wt[w] = g.wide.size();
+    for (auto& o : of) {
+        for (auto* t : o) g.wide.push_back(t->to);
+        g.wide.resize(g.wide.size() + WIDE_OWN - o.size(), -1);
+        g.gm.own[w] = std::max(g.gm.own[w], (int)o.size());
+    }
+    g.wo[w] = g.wide.size();
+    for (auto& o : of) {
+        g.wide.push_back((int32_t)g.wl.size());
+        const size_t first = g.wl.size();
+        for (size_t q = 0; q < o.size(); ++q)
+            for (uint32_t c : o[q]->c) g.wl.push_back((c & 0x7FFF) | (uint32_t)q << 16 | (c & 0x8000) << 16);
+        std::stable_sort(g.wl.begin() + first, g.wl.end(), [](uint32_t a, uint32_t b) { return (a & 0x7FFF) < (b & 0x7FFF); });
+    }
+    g.wide.push_back((int32_t)g.wl.size());
+    g.xs[w] = g.wide.size();
+    g.wide.insert(g.wide.end(), xs.begin(), xs.end());
+}
+
 }  // namespace
 
 void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std::vector<FallRec>& fall,
@@ -302,6 +362,9 @@ void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std:
             }
         }
     }
+    for (int w = 2; w <= 8; ++w) deal(sp, w, g);
+    g.wl.insert(g.wl.end(), 64, 0);
+    gm.lds_max = (int)lds_max;
     cut(sp, 16, false, (uint32_t)nr, g.sl);
     cut(br, 16, false, (uint32_t)gm.zero << 3, g.bl);
     cut(col, 32, false, (uint32_t)gm.zero << 3, g.cl);

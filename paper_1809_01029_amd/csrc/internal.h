@@ -244,7 +244,18 @@ struct GatherMech {
     const PJ_GLOBAL uint4* jm;       // [groups][64] {entry, 6 contributions}
     const PJ_GLOBAL uint4* jl;       // [pairs][64] {entry, 2 contributions} of two groups
     const PJ_GLOBAL JacRound* rounds;
+    // wide kernel: the species' sums again, long ones in parts, dealt to the waves;
+    // tables for 2 w waves from [w]: what wave v's sum o is (species, ns + index of a
+    // further part, or -1) at [v * WIDE_OWN + o], the wave's words [wo[v], wo[v + 1]),
+    // and the further parts of each species [xs[k], xs[k + 1]).  Words: reaction
+    // (ascending) | o << 16 | minus << 31, and 64 more after the last.
+    int own[9], lds_max;
+    const PJ_GLOBAL int32_t* wt[9];
+    const PJ_GLOBAL int32_t* wo[9];
+    const PJ_GLOBAL int32_t* xs[9];
+    const PJ_GLOBAL uint32_t* wl;
 };
+constexpr int WIDE_OWN = 16;         // most sums of a wave of the wide kernel
 constexpr int GATHER_BLOCKS = 5;     // most 64-reaction blocks of a wave
 enum GatherMode : int { GM_SRC = 0, GM_JAC = 1, GM_DENSE = 2, GM_ADJ = 3 };
 
@@ -348,6 +359,9 @@ struct GatherImage {
     } sl, bl, cl, jh;
     std::vector<uint4> jm, jl;
     std::vector<JacRound> rounds;
+    std::vector<int32_t> wide;             // wt, wo and xs from [w] of each number of waves
+    std::vector<uint32_t> wl;
+    size_t wt[9] = {}, wo[9] = {}, xs[9] = {};
 };
 void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std::vector<FallRec>& fall,
                   const std::vector<int32_t>& dense_rows,
@@ -370,6 +384,7 @@ hipError_t launch_gather(const GatherCall& c);
 hipError_t launch_gather_ext(const GatherCall& c);
 // wide.hip, wide_ext.hip (wide_body.h)
 int64_t wide_lds(const GatherMech& gm, int waves);
+bool wide_fits(const GatherMech& gm, int waves);
 hipError_t launch_wide(const GatherCall& c);
 hipError_t launch_wide_ext(const GatherCall& c);
 

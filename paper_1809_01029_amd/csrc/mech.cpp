@@ -590,7 +590,7 @@ pj_status upload_mechanism(Mechanism& m, std::string& err) {
         o_list[q][3] = place(vbytes(gl[q]->more));
     }
     size_t o_jm = place(vbytes(gi.jm)), o_jl = place(vbytes(gi.jl)), o_rounds = place(vbytes(gi.rounds)),
-           o_gm = place(sizeof(GatherMech));
+           o_wide = place(vbytes(gi.wide)), o_wl = place(vbytes(gi.wl)), o_gm = place(sizeof(GatherMech));
     std::vector<unsigned char> host(total, 0);
     auto put = [&](size_t off, const void* src, size_t bytes) { std::memcpy(host.data() + off, src, bytes); };
     put(o_th, th.data(), th.size() * sizeof(ThermoRec));
@@ -624,6 +624,8 @@ pj_status upload_mechanism(Mechanism& m, std::string& err) {
     putv(o_jm, gi.jm);
     putv(o_jl, gi.jl);
     putv(o_rounds, gi.rounds);
+    putv(o_wide, gi.wide);
+    putv(o_wl, gi.wl);
 
     void* d = nullptr;
     if (hipMalloc(&d, total) != hipSuccess) { err = "hipMalloc of the mechanism tables failed"; return PJ_E_DEVICE; }
@@ -653,6 +655,13 @@ pj_status upload_mechanism(Mechanism& m, std::string& err) {
     gm.jm = gptr((const uint4*)P(o_jm));
     gm.jl = gptr((const uint4*)P(o_jl));
     gm.rounds = gptr((const JacRound*)P(o_rounds));
+    for (int w = 0; w < 9; ++w) {
+        const int32_t* const t = (const int32_t*)P(o_wide);
+        gm.wt[w] = gptr(t + gi.wt[w]);
+        gm.wo[w] = gptr(t + gi.wo[w]);
+        gm.xs[w] = gptr(t + gi.xs[w]);
+    }
+    gm.wl = gptr((const uint32_t*)P(o_wl));
     put(o_gm, &gm, sizeof(gm));
     m.d_gm = (const GatherMech*)P(o_gm);
     if (hipMemcpy(d, host.data(), total, hipMemcpyHostToDevice) != hipSuccess) {

@@ -4,23 +4,29 @@
 //
 // All lanes of a wave work on the same reaction: its record sits in scalar
 // registers, a falloff or third-body reaction costs only its own step, and every
-// LDS access is a row of 64 consecutive states, without bank conflicts (an LDS
-// FP64 atomic takes 8 cycles so, 17 to 26 at the addresses of kernel_body.h).
+// LDS access is a row of 64 consecutive states, without bank conflicts.
 // Rates as in gather_body.h: single-molecule slots, reverse rates from one
-// exponential per species.  The LDS holds four rows a species,
+// exponential per species.  The LDS holds two rows a species,
 //
-//   C_k, exp(g_k), exp(-g_k), wdot_k
+//   C_k, exp(g_k)
 //
-// (exp(g) rows hold g where the product of ratios could leave the range);
-// enthalpies are evaluated again at the end rather than kept.
+// (the latter g_k where the product of ratios could leave the range), and the
+// rates of progress of the reactions that the waves evaluate between two
+// barriers; enthalpies are evaluated again at the end rather than kept.
 //
-// What bounds it: FP64 arithmetic.  53 species, 325 reactions, 1048576 states,
-// CONP, layout C: 2.41 ms (scatter kernel, 4 states and one wave a workgroup:
-// 3.51), about 700 vector instructions a state, half of them the elementary
-// part of the rates, a fifth 24 Troe reactions; 110 kB of LDS hold one workgroup
-// of 16 waves a compute unit (8 waves 2.94, 4 waves 4.41 ms).  Two reactions go
-// through their exponentials together, which a wave alone would wait for (2.74
-// ms one after the other).  13 species, 27 reactions: 0.29 ms (0.86).
+// Every sum is formed in a fixed order: the waves write their rates of progress to
+// LDS, and each sums its own species over a static list.  Waves that add to
+// shared rows with atomics (which need a third row) take 2.42 ms where this takes
+// 2.52, but in an order, and with last bits, that vary from run to run; waves that
+// add in turn 4.39 ms.
+//
+// What bounds it: issue of FP64 and, a quarter of the time, of the sums'
+// instructions (without the sums 1.95 ms).  53 species, 325 reactions, 1048576
+// states, CONP, layout C: 2.52 ms (scatter kernel, 4 states and one wave a
+// workgroup: 3.50).  78 kB of LDS let two workgroups of 8 waves share a compute
+// unit, one evaluating while the other sums (one of 16 waves 3.23 ms, 4 waves
+// 3.38).  Two reactions go through their exponentials together, which a wave alone
+// would wait for.  13 species, 27 reactions, 262144 states: 0.09 ms (0.22).
 #pragma once
 
 #include "gather_body.h"
@@ -34,29 +40,52 @@ namespace {
 
 constexpr int WIDE_STATES = 64;
 
-enum { F_C = 0, F_E = 1, F_I = 2, F_W = 3, WIDE_ROWS = 4 };
+// (once the reactions are done, the production rates take the rows of the
+// exponentials, the further parts of their sums those of the concentrations: at
+// most one for every species but the bath gas)
+enum { F_C = 0, F_E = 1, F_W = F_E, F_X = F_C, WIDE_ROWS = 2 };
 constexpr int WIDE_THREADS = 1024;
 // (at the end T's row holds dT/dt)
 enum { WS_T = 0, WS_V, WS_P, WS_SDOT, WS_N };
 
 // LDS of a workgroup in doubles: species records (one double longer than their
-// rows: reads and writes along the species meet different banks; two for each
-// wave at least, which pass partial sums through rows not in use), scalars of
-// the states, powers of P0/RT, flags of the waves
-inline int64_t wide_doubles(int ns, int waves) {
-    const int records = ns + 1 > 2 * waves ? ns + 1 : 2 * waves;
-    return (int64_t)records * (WIDE_ROWS * WIDE_STATES + 1) + (WS_N + 7) * WIDE_STATES + (waves + 1) / 2;
+// rows: reads and writes along the species meet different banks), scalars of the
+// states, powers of P0/RT, the rates of progress of a stage (four rows a wave and
+// batch, and one of zeros; also the partial sums that waves pass to each other),
+// flags of the waves
+inline int64_t wide_doubles(int ns, int waves, int batches) {
+    return (int64_t)(ns + 1) * (WIDE_ROWS * WIDE_STATES + 1) + (WS_N + 7 + 4 * waves * batches + 1) * WIDE_STATES +
+           (waves + 1) / 2;
+}
+// Batches of a stage: as many as the LDS holds without costing a workgroup of a
+// compute unit (which holds 16 waves).
+inline int wide_batches(const GatherMech& gm, int waves) {
+    const int all = (gm.nr + 4 * waves - 1) / (4 * waves);
+    const int64_t least = wide_doubles(gm.ns, waves, 1) * 8;
+    const int64_t groups = std::max<int64_t>(1, std::min<int64_t>(gm.lds_max / least, 16 / waves));
+    int n = 1;
+    while (n < all && wide_doubles(gm.ns, waves, n + 1) * 8 <= gm.lds_max / groups) ++n;
+    return n;
 }
 
-template <int FORM, int LAYOUT, int S, bool EXT>
+// OWN: the most sums of a wave
+// 1 / x for a normal x with a normal reciprocal: two Newton steps from the
+// hardware's estimate
+__device__ inline double reciprocal(double x) {
+    double y = __builtin_amdgcn_rcp(x);
+    y = fma(y, fma(-x, y, 1.0), y);
+    return fma(y, fma(-x, y, 1.0), y);
+}
+
+template <int FORM, int LAYOUT, int OWN, bool EXT>
 __global__ void __launch_bounds__(WIDE_THREADS) __attribute__((amdgpu_waves_per_eu(PJ_WPE_WIDE)))
-pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const long g1, const unsigned per,
+pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const long g1, const unsigned per, const int stage,
                const double* __restrict__ state, const double* __restrict__ param, double* __restrict__ dstate,
                const double* __restrict__ arr) {
     extern __shared__ double lds[];
     const long qg = g0 + (long)(blockIdx.x & 7) * per + (blockIdx.x >> 3);
     if (qg >= g1) return;
-    constexpr int REC = WIDE_ROWS * S + 1;    // doubles of a species
+    constexpr int S = WIDE_STATES, REC = WIDE_ROWS * S + 1;    // doubles of a species
     GatherPtr gm = (GatherPtr)gmp;
     const int ns = gm->ns, nr = gm->nr, N = ns + 1, bath = ns - 1;
     const int tid = threadIdx.x, nthr = blockDim.x;
@@ -64,9 +93,11 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
     static_assert(S == 64, "a lane per state");
     const int s = lane, g = wave, G = nwave;              // state; of the threads of a state
     double* const sp = lds;
-    double* const sc = sp + (ns + 1 > 2 * G ? ns + 1 : 2 * G) * REC;
+    double* const sc = sp + (ns + 1) * REC;
     double* const pw = sc + WS_N * S;
-    int* const ints = reinterpret_cast<int*>(pw + 7 * S);
+    double* const qr = pw + 7 * S;
+    const int rows = 4 * G * stage;                       // rates of progress of a stage
+    int* const ints = reinterpret_cast<int*>(qr + (rows + 1) * S);
     auto at_ = [&](int k, int f) -> double& { return sp[k * REC + f * S + s]; };
 
     // ---- states into the C rows (moles) and the scalars
@@ -135,8 +166,6 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
         odd |= !(gk >= G_MIN && gk <= G_MAX);
         const double e = fexp(gk);
         at_(k, F_E) = e;
-        at_(k, F_I) = 1.0 / e;
-        if (k >= 2 * G) at_(k, F_W) = 0.0;
         const double cp = t.c[0] + T * (t.c[1] + T * (t.c[2] + T * (t.c[3] + T * t.c[4])));
         const double chat = FORM == PJ_CONP ? cp : cp - 1.0;
         if (k < bath) {
@@ -148,13 +177,13 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
             cb_chat = chat;
         }
     }
-    // (partial sums in the first 2 G wdot rows)
-    at_(2 * g, F_W) = acc.hi;
-    at_(2 * g + 1, F_W) = acc.lo;
+    auto part = [&](int i) -> double& { return qr[i * S + s]; };
+    part(2 * g) = acc.hi;
+    part(2 * g + 1) = acc.lo;
     if (tid < S) {
         // an empty slot's species, powers of P0/RT
-        at_(ns, F_C) = at_(ns, F_E) = at_(ns, F_I) = 1.0;
-        if (ns >= 2 * G) at_(ns, F_W) = 0.0;
+        at_(ns, F_C) = at_(ns, F_E) = 1.0;
+        part(rows) = 0.0;
         const double x = PREF / (RU * T), ix = (RU * T) / PREF;
         pw[0 * S + s] = x * x * x;
         pw[1 * S + s] = x * x;
@@ -175,10 +204,7 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
     if (tid < S) {
         // n_Ns = P V / (R T) - RN(sum of the others)
         dd a{0.0, 0.0};
-        for (int q = 0; q < G; ++q) {
-            a = dd_add(a, dd{at_(2 * q, F_W), at_(2 * q + 1, F_W)});
-            at_(2 * q, F_W) = at_(2 * q + 1, F_W) = 0.0;
-        }
+        for (int q = 0; q < G; ++q) a = dd_add(a, dd{part(2 * q), part(2 * q + 1)});
         at_(bath, F_C) = ((P * Vv) / (RU * T) - a.hi) / Vv;
     }
     double lnP = 0.0;
@@ -269,7 +295,7 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
         for (int a = 0; a < NSLOT; ++a) {
             // (an empty slot reads the empty species' ones)
             r.c[a] = row(r.off[a], F_C);
-            r.x[a] = row(r.off[a], a < MAXSIDE ? F_I : F_E);
+            r.x[a] = row(r.off[a], F_E);
         }
         r.pw = pw[((r.w >> 8) & 7) * S + s];
         return r;
@@ -286,7 +312,7 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
         const V2 Pb = both([](const Rxn& r) { return r.w & GI_REV ? r.c[3] * r.c[4] * r.c[5] : 0.0; });
         // (an irreversible reaction's is 0: its product may overflow with k_f, and inf * 0 is NaN)
         const V2 kq = both([](const Rxn& r) {
-            return r.w & GI_REV ? ((r.x[0] * r.x[3]) * (r.x[1] * r.x[4]) * (r.x[2] * r.x[5])) * r.pw : 0.0;
+            return r.w & GI_REV ? (r.x[3] * r.x[4] * r.x[5]) * reciprocal(r.x[0] * r.x[1] * r.x[2]) * r.pw : 0.0;
         });
         q = kf * Pf - (kf * kq) * Pb;
     };
@@ -306,10 +332,10 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
             double dG = 0.0;
             if (logs) {
 #pragma unroll
-                for (int a = 0; a < NSLOT; ++a) dG += a < MAXSIDE ? -row(r.off[a], F_E) : r.x[a];
+                for (int a = 0; a < NSLOT; ++a) dG += a < MAXSIDE ? -r.x[a] : r.x[a];
                 dG -= (double)((int)((w >> 8) & 7) - 3) * lnP;
             } else {
-                dG = log(((r.x[0] * r.x[3]) * (r.x[1] * r.x[4]) * (r.x[2] * r.x[5])) * r.pw);
+                dG = log((r.x[3] * r.x[4] * r.x[5]) / (r.x[0] * r.x[1] * r.x[2]) * r.pw);
             }
             q = fexp(lnkf) * (r.c[0] * r.c[1] * r.c[2]);
             if (w & GI_REV) q -= fexp(lnkf + dG) * (r.c[3] * r.c[4] * r.c[5]);
@@ -339,19 +365,46 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
         }
         return q;
     };
-    // (an empty slot adds to the empty species; the third ones are mostly empty)
-    auto put = [&](const Rxn& r, double q) {
-        atomicAdd(&row(r.off[0], F_W), -q);
-        atomicAdd(&row(r.off[1], F_W), -q);
-        if (((r.w >> 12) & 3) > 2) atomicAdd(&row(r.off[2], F_W), -q);
-        atomicAdd(&row(r.off[3], F_W), q);
-        atomicAdd(&row(r.off[4], F_W), q);
-        if (((r.w >> 14) & 3) > 2) atomicAdd(&row(r.off[5], F_W), q);
+    // Production rates: the rates of progress of `stage` batches go to rows in LDS,
+    // then each wave adds the words of its sums, by ascending reaction: no addition
+    // depends on the order of the waves.  The sums wait in registers, found by an index
+    // that the wave shares; 64 words are loaded a stage ahead, four rows read at a time
+    // (53 species, 1048576 states: 2.54 ms; eight 2.58, twelve 2.61).
+    const PJ_GLOBAL uint32_t* const words = (const PJ_GLOBAL uint32_t*)gm->wl;
+    typedef double Sums __attribute__((ext_vector_type(OWN)));
+    Sums sum = 0.0;
+    int cur = uniform_load(gm->wo[nwave >> 1], wave);
+    const int last = uniform_load(gm->wo[nwave >> 1], wave + 1);
+    uint32_t wv = at(words, (uint32_t)(cur + lane));
+    auto sums = [&](int p0) {
+        for (;;) {
+            // of 64 words those of the wave and the stage: row's offset, sum and sign;
+            // the others the row of zeros
+            const bool in = lane < last - cur && (int)(wv & 0x7FFF) < p0 + rows;
+            const int n = __builtin_popcountll(__ballot(in));
+            const uint32_t x = (in ? (wv & 0x7FFF) - (uint32_t)p0 : (uint32_t)rows) * (S * 8) | (wv >> 15 & 62) | (wv & 0x80000000u);
+            for (int j = 0; j < n; j += 4) {
+                double v[4];
+                uint32_t u[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    u[c] = word(x, j + c);
+                    v[c] = *reinterpret_cast<const double*>(reinterpret_cast<const char*>(qr) + ((u[c] & 0x7FFFFE00u) | (uint32_t)(8 * s)));
+                }
+                PJ_READS_FIRST();
+#pragma unroll
+                for (int c = 0; c < 4; ++c) sum[(u[c] & 62) >> 1] += sign31(u[c]) * v[c];
+            }
+            cur += n;
+            wv = at(words, (uint32_t)(cur + lane));
+            if (n < 64) break;
+        }
     };
     {
         uint32_t rec0 = rec_words(0), rec1 = rec_words(1);
         Extra ex0 = extra(0, rec0);
-        for (int b = 0; b < nbatch; ++b) {
+        const int nb = (nr + 4 * nwave - 1) / (4 * nwave);      // (of the first wave: all meet at the barriers)
+        for (int b = 0, t = 0; b < nb; ++b) {
             const uint32_t rec = rec0;
             const Extra ex = ex0;
             rec0 = rec1;
@@ -363,10 +416,27 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
                 PJ_READS_FIRST();
                 V2 lnkf, q;
                 rates(r0, r1, lnkf, q);
-                put(r0, rate(r0, rec, ex, l, lnkf[0], q[0]));
-                put(r1, rate(r1, rec, ex, l + 16, lnkf[1], q[1]));
+                q[0] = rate(r0, rec, ex, l, lnkf[0], q[0]);
+                q[1] = rate(r1, rec, ex, l + 16, lnkf[1], q[1]);
+                // the stage before has been added by all
+                if (t == 0 && l == 0) __syncthreads();
+                part(wave + nwave * (4 * t + (l >> 4))) = q[0];
+                part(wave + nwave * (4 * t + (l >> 4) + 1)) = q[1];
+            }
+            if (++t == stage || b + 1 == nb) {
+                __syncthreads();
+                sums(4 * nwave * (b + 1 - t));
+                t = 0;
             }
         }
+    }
+    // (every wave is past its last reaction)
+#pragma unroll
+    for (int o = 0; o < OWN; ++o) {
+        const int to = uniform_load(gm->wt[nwave >> 1], wave * WIDE_OWN + o);
+        if (to < 0) continue;
+        if (to < ns) at_(to, F_W) = sum[o];
+        else at_(to - ns, F_X) = sum[o];
     }
     __syncthreads();
 
@@ -374,22 +444,25 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
     gm = fresh(gm);
     double np = 0.0, om = 0.0;
     for (int k = g; k < ns; k += G) {
-        const double wk = at_(k, F_W), h = enthalpy(record(k));
+        double wk = at_(k, F_W);
+        const int x0 = uniform_load(gm->xs[nwave >> 1], k), x1 = uniform_load(gm->xs[nwave >> 1], k + 1);
+        for (int x = x0; x < x1; ++x) wk += at_(x, F_X);
+        if (x1 > x0) at_(k, F_W) = wk;
+        const double h = enthalpy(record(k));
         np += (FORM == PJ_CONP ? h : h - 1.0) * wk;
         om += at(gm->wfac, (uint32_t)k) * wk;
         if (k == bath) Dp += at_(k, F_C) * cb_chat;
     }
-    // (through rows of the exponentials, no longer needed)
-    at_(g, F_E) = np;
-    at_(g, F_I) = om;
-    at_(G + g, F_E) = Dp;
+    part(g) = np;
+    part(G + g) = om;
+    part(2 * G + g) = Dp;
     __syncthreads();
     if (tid < S) {
         np = om = Dp = 0.0;
         for (int q = 0; q < G; ++q) {
-            np += at_(q, F_E);
-            om += at_(q, F_I);
-            Dp += at_(G + q, F_E);
+            np += part(q);
+            om += part(G + q);
+            Dp += part(2 * G + q);
         }
         const double Tdot = -T * np / Dp;
         sc[WS_T * S + s] = Tdot;
@@ -415,10 +488,11 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
 
 // (c.waves pairs of waves: a workgroup fills a compute unit with its LDS long
 // before 8 waves fill the SIMDs)
-template <int FORM, int LAYOUT, bool EXT>
+template <int FORM, int LAYOUT, int OWN, bool EXT>
 static hipError_t launch_wide_t(const GatherCall& c) {
-    auto k = pj_wide_source<FORM, LAYOUT, WIDE_STATES, EXT>;
-    const int64_t lds = wide_lds(*c.gm, c.waves);
+    auto k = pj_wide_source<FORM, LAYOUT, OWN, EXT>;
+    const int stage = wide_batches(*c.gm, 2 * c.waves);
+    const int64_t lds = wide_doubles(c.gm->ns, 2 * c.waves, stage) * 8;
     if (lds > 65536) {
         static std::atomic<uint64_t> done{0};
         hipError_t e = allow_full_lds((const void*)k, done);
@@ -429,7 +503,7 @@ static hipError_t launch_wide_t(const GatherCall& c) {
     for (int64_t g0 = 0; g0 < groups; g0 += most) {
         const int64_t g1 = groups < g0 + most ? groups : g0 + most, per = (g1 - g0 + 7) / 8;
         hipLaunchKernelGGL(k, dim3((unsigned)(8 * per)), dim3(128 * c.waves), (size_t)lds, c.stream, c.d_gm, (long)c.n,
-                           (long)g0, (long)g1, (unsigned)per, c.state, c.param, c.dstate, c.arr);
+                           (long)g0, (long)g1, (unsigned)per, stage, c.state, c.param, c.dstate, c.arr);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -438,8 +512,10 @@ static hipError_t launch_wide_t(const GatherCall& c) {
 
 template <bool EXT>
 hipError_t launch_wide_impl(const GatherCall& c) {
+    const bool few = c.gm->own[c.waves] <= 8;
 #define PJ_W(F, L) \
-    if (c.form == F && c.layout == L) return launch_wide_t<F, L, EXT>(c);
+    if (c.form == F && c.layout == L) \
+        return few ? launch_wide_t<F, L, 8, EXT>(c) : launch_wide_t<F, L, WIDE_OWN, EXT>(c);
     PJ_W(PJ_CONP, PJ_LAYOUT_C) PJ_W(PJ_CONP, PJ_LAYOUT_F) PJ_W(PJ_CONV, PJ_LAYOUT_C) PJ_W(PJ_CONV, PJ_LAYOUT_F)
 #undef PJ_W
     return hipErrorInvalidValue;
