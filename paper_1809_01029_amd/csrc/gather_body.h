@@ -27,10 +27,11 @@
 // results are bitwise reproducible at any launch shape.
 //
 // Reverse rates: kr / kf = prod exp(g_k)^nu (P0/RT)^-dnu from one exponential
-// per species in place of one per reaction.  The product of three ratios
-// stays in range while every g_k lies in [-160, 60]; a group of states with
-// one outside (low temperatures) takes the exponential of the sum instead, and
-// so does a reaction whose kf itself would underflow.
+// per species in place of one per reaction.  A reaction whose product leaves the
+// range of normal numbers, or whose kf would, takes the product of the mantissas
+// and the sum of the exponents instead (scaled_exp); a state with a |g_k| above
+// 700, whose exponential alone is out of range, the exponential of the sum.  Either
+// is decided for each state by itself: its results don't depend on its neighbours.
 //
 // A workgroup evaluates NV states, NV compile-time; every lane works for all
 // of them, except that in a Jacobian each wave takes the reactions of one
@@ -70,7 +71,7 @@ namespace {
 
 // per-state scalars in LDS
 enum { SC_LNT = 0, SC_NSUM, SC_CB, SC_ICB, SC_DP, SC_DDP, SC_TT, SC_TS, SC_ST, SC_SS, SC_TDOT, SC_SDOT, SC_OM, SC_SCW,
-       SC_T, SC_V, SC_P, SC_INVT, SC_INVV, SC_INVRT, SC_CTOT, SC_LNP,
+       SC_T, SC_V, SC_P, SC_INVT, SC_INVV, SC_INVRT, SC_CTOT,
        SC_KAP, SC_VT, SC_VS, SC_LB, SC_N };
 // fields of a species record in LDS: {exp g, C, exp -g, h, chat/R}, after the
 // reactions {wdot, 1/C, T column sum, h, chat/R}; the adjoint's also {what a unit
@@ -80,8 +81,10 @@ enum { SC_LNT = 0, SC_NSUM, SC_CB, SC_ICB, SC_DP, SC_DDP, SC_TT, SC_TS, SC_ST, S
 // Jacobian, whose lists read single fields, an array each (8.65 ms against 9.28).
 enum { A_E = 0, A_C = 1, A_I = 2, A_H = 3, A_CP = 4, A_Y = 5, A_VV = 6, A_W = 0, A_IC = 1, A_VT = 2 };
 constexpr double C_TINY = 1e-150;
-constexpr double G_MIN = -160.0, G_MAX = 60.0;
-constexpr double LNK_MIN = -690.0;
+// |g| up to which one exponential is a normal number, and six together are
+constexpr double G_FAR = 700.0, G_CALM = 115.0;
+constexpr double LNK_FAR = 690.0;
+__device__ inline bool normal(double x) { return __builtin_amdgcn_class(x, 0x108); }
 
 // The description is read through a pointer into constant memory, made opaque
 // again for each phase: its fields then are scalar loads where they are used
@@ -156,6 +159,16 @@ __device__ inline double fexp_in(double x) {
     q = fma(q, r, sconst(0x1.5555555555556p-3));
     q = fma(q, r, 0.5);
     return ldexp(1.0 + fma(r * r, q, r), (int)n);
+}
+// m 2^e exp(x) where the parts may be out of range, for m in [1e-8, 1e8], |e| <
+// 2^13
+__device__ inline double scaled_exp(double x, double m, int e) {
+    const double c = fmin(fmax(x, -1e4), 1e4);
+    const double n = __builtin_rint(c * 0x1.71547652b82fep+0);
+    double r = fma(-n, 0x1.62e42fefa39efp-1, c);
+    r = fma(-n, 0x1.abc9e3b39803fp-56, r);
+    const double y = ldexp(fexp_in(r) * m, (int)n + e);
+    return x != x ? x : y;
 }
 __device__ inline double fexp(double x) {
     double y = fexp_in(x);
@@ -383,7 +396,8 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
 
     // ---- (1) closure (wave 0), thermodynamics (the others; with one wave all)
     const int tb = nwave > 1 ? 64 : 0;
-    bool odd_c = false, odd_g = false;
+    bool odd_c = false, wild_g = false;
+    int far_g = 0;                               // by state
     // (a state past the end computes a copy of the last)
     auto clamp_state = [&](int v) { const long q = qg * NV + v; return q < n ? q : n - 1; };
     auto X = [&](long sc, int i) -> double { return layout == PJ_LAYOUT_F ? state[(long)i * n + sc] : state[sc * (long)N + i]; };
@@ -468,10 +482,11 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         }
     }
     // one species of one state per lane
-    auto thermo = [&](bool logs) {
+    auto thermo = [&](int logs) {
         const GatherPtr gm = fresh(gmp);
         for (int it = tid - tb; it < ns * NV; it += nthr - tb) {
             const int k = NV == 1 ? it : it / NV, v = NV == 1 ? 0 : it - k * NV;
+            if (logs && !((logs >> v) & 1)) continue;
             const long sc = clamp_state(v);
             const double T = X(sc, 0);
             const int rg = T < at(gm->tmid, (uint32_t)k) ? 0 : 1;
@@ -499,10 +514,10 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             const double h = a0 + T * (a(5) + T * (a(6) + T * (a(7) + T * a(8)))) + a(12) * invT;
             const double sr = a0 * lnT + T * (a1 + T * (a(9) + T * (a(10) + T * a(11)))) + a(13);
             const double g = h - sr;
-            odd_g |= !(g >= G_MIN && g <= G_MAX);
+            wild_g |= !(fabs(g) <= G_CALM);
+            if (!(fabs(g) <= G_FAR)) far_g |= 1 << v;
             if (logs) {
                 A[fld(k, A_E) * NV + v] = g;
-                if (k == 0) SC[SC_LNP * NV + v] = log(PREF / (RU * T));
             } else {
                 const double e = fexp(g);
                 A[fld(k, A_E) * NV + v] = e;
@@ -514,20 +529,23 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             }
         }
     };
-    if (tid >= tb) thermo(false);
+    if (tid >= tb) thermo(0);
     {
-        const int f = (__ballot(odd_g) ? 1 : 0) | (__ballot(odd_c) ? 2 : 0);
+        int f = (__ballot(odd_c) ? 1 << NV : 0) | (__ballot(wild_g) ? 2 << NV : 0);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) f |= __ballot((far_g >> v) & 1) ? 1 << v : 0;
         if (lane == 0) ints[wave] = f;
     }
     __syncthreads();
     int flags = 0;
     for (int w = 0; w < nwave; ++w) flags |= ints[w];
     flags = __builtin_amdgcn_readfirstlane(flags);
-    const bool logs = flags & 1, tiny = flags & 2;
+    const int logs = flags & ((1 << NV) - 1);       // states whose reactions take the exponential of the sum
+    const bool tiny = (flags >> NV) & 1, calm = !((flags >> NV) & 2);
     if (logs) {
-        // some g out of range: exponentials of the sums, from g itself
-        if (tid >= tb) thermo(true);
-        if (tid < NV) A[fld(ns, A_E) * NV + tid] = 0.0;
+        // g itself in place of its exponential
+        if (tid >= tb) thermo(logs);
+        if (tid < NV && (logs >> tid) & 1) A[fld(ns, A_E) * NV + tid] = 0.0;
         __syncthreads();
     }
 
@@ -580,12 +598,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         auto U = [&](int q) { return RN == 1 ? vmap(K(q), [](double x) { return uniform(x); }) : K(q); };
         const V T = U(SC_T), lnT = U(SC_LNT), invT = U(SC_INVT), Ctot = U(SC_CTOT);
         const int b3 = DER ? gm->b3 : 0, neff_rec = gm->neff;
-        auto vlow = [](const V& x) {
-            bool b = false;
-#pragma unroll
-            for (int v = 0; v < RN; ++v) b |= x[v] < LNK_MIN;
-            return b;
-        };
+        auto far = [&](int v) { return ((logs >> (RN == NV ? v : rst)) & 1) != 0; };
         // sums over reactions: dE dq/dT, dE dq/dS, dOmega dq/dT, dOmega dq/dS;
         // adjoint: lambda dq/dT, lambda dq/dS, lambda dq/dC_Ns, then the energy, mole,
         // heat capacity and (CONP) v weighted rates
@@ -626,7 +639,10 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 }
             }
             // slots: concentration products, ratio kr / kf, dH
-            V Pf = 1.0, Pb = 1.0, kq = 1.0, dH = 0.0, dG = 0.0, Pft = 1.0, Pbt = 1.0, lam = 0.0, dcp = 0.0, dvv = 0.0;
+            V Pf = 1.0, Pb = 1.0, kq = 1.0, dH = 0.0, Pft = 1.0, Pbt = 1.0, lam = 0.0, dcp = 0.0, dvv = 0.0;
+            bool fits[RN];       // the product of the exponentials is precise
+#pragma unroll
+            for (int v = 0; v < RN; ++v) fits[v] = true;
             {
                 V xs[NSLOT][3];
 #pragma unroll
@@ -643,7 +659,13 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 PJ_READS_FIRST();
                 Pf = xs[0][0] * xs[1][0] * xs[2][0];
                 Pb = xs[3][0] * xs[4][0] * xs[5][0];
-                kq = (xs[0][1] * xs[3][1]) * (xs[1][1] * xs[4][1]) * (xs[2][1] * xs[5][1]);
+                const V k0 = xs[0][1] * xs[3][1], k1 = xs[1][1] * xs[4][1], k2 = xs[2][1] * xs[5][1], k01 = k0 * k1;
+                kq = k01 * k2 * vec(PW, (w >> 8) & 7);
+                if (!calm)
+#pragma unroll
+                    for (int v = 0; v < RN; ++v)
+                        fits[v] = normal(k0[v]) && normal(k1[v]) && normal(k2[v]) && normal(k01[v]) && normal((k01 * k2)[v]) &&
+                                  normal(kq[v]);
                 if (DER) dH = ((xs[3][2] - xs[0][2]) + (xs[4][2] - xs[1][2])) + (xs[5][2] - xs[2][2]);
                 if (DER && tiny) {
                     // absent species at 1e-150
@@ -672,15 +694,40 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 dcp = delta(1);
                 if (FORM == PJ_CONP) dvv = delta(2);
             }
-            if (logs)
-#pragma unroll
-                for (int a = 0; a < NSLOT; ++a)
-                    if ((cm >> a) & 1) dG += a < MAXSIDE ? -SP(rr.sp[a], A_E) : SP(rr.sp[a], A_E);
             const double dnu = (double)((int)((w >> 8) & 7) - 3);
             const V kf = vexp(lnkf);
-            V kr = kf * (kq * vec(PW, (w >> 8) & 7));
-            if (logs) kr = vexp(lnkf + dG - dnu * K(SC_LNP));
-            else if (__any(vlow(lnkf))) kr = vexp(lnkf + vmap(kq * vec(PW, (w >> 8) & 7), [](double y) { return log(y); }));
+            V kr = kf * kq;
+            bool bad[RN], some = false;
+#pragma unroll
+            for (int v = 0; v < RN; ++v) {
+                bad[v] = rev && (!fits[v] || far(v) || !(fabs(lnkf[v]) < LNK_FAR));
+                some |= bad[v];
+            }
+            if (__any(some)) {
+#pragma unroll
+                for (int v = 0; v < RN; ++v) {
+                    double x = lnkf[v], m = vec(PW, (w >> 8) & 7)[v];
+                    int e = 0;
+                    if (far(v)) {
+                        x -= dnu * log(PREF / (RU * K(SC_T)[v]));
+                        m = 1.0;
+                    }
+#pragma unroll
+                    for (int a = 0; a < NSLOT; ++a)
+                        if ((cm >> a) & 1) {
+                            if (far(v)) {
+                                const double g = SP(rr.sp[a], A_E)[v];
+                                x += a < MAXSIDE ? -g : g;
+                            } else {
+                                const double y = SP(rr.sp[a], a < MAXSIDE ? A_I : A_E)[v];
+                                m *= __builtin_amdgcn_frexp_mant(y);
+                                e += __builtin_amdgcn_frexp_exp(y);
+                            }
+                        }
+                    x = scaled_exp(x, m, e);
+                    kr[v] = bad[v] ? x : kr[v];
+                }
+            }
             if (!rev) kr = 0.0;
             const V Rf = kf * Pf;
             const V Rr = kr * Pb;

@@ -10,7 +10,7 @@
 //
 //   C_k, exp(g_k)
 //
-// (the latter g_k where the product of ratios could leave the range), and the
+// (the latter g_k in a state where one exceeds 700), and the
 // rates of progress of the reactions that the waves evaluate between two
 // barriers; enthalpies are evaluated again at the end rather than kept.
 //
@@ -55,7 +55,7 @@ enum { WS_T = 0, WS_V, WS_P, WS_SDOT, WS_N };
 // flags of the waves
 inline int64_t wide_doubles(int ns, int waves, int batches) {
     return (int64_t)(ns + 1) * (WIDE_ROWS * WIDE_STATES + 1) + (WS_N + 7 + 4 * waves * batches + 1) * WIDE_STATES +
-           (waves + 1) / 2;
+           2 * waves;
 }
 // Batches of a stage: as many as the LDS holds without costing a workgroup of a
 // compute unit (which holds 16 waves).
@@ -97,7 +97,7 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
     double* const pw = sc + WS_N * S;
     double* const qr = pw + 7 * S;
     const int rows = 4 * G * stage;                       // rates of progress of a stage
-    int* const ints = reinterpret_cast<int*>(qr + (rows + 1) * S);
+    uint64_t* const masks = reinterpret_cast<uint64_t*>(qr + (rows + 1) * S);     // states, of each wave
     auto at_ = [&](int k, int f) -> double& { return sp[k * REC + f * S + s]; };
 
     // ---- states into the C rows (moles) and the scalars
@@ -159,11 +159,12 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
     };
     dd acc{0.0, 0.0};
     double Dp = 0.0, cb_chat = 0.0;
-    bool odd = false;
+    bool odd = false, calm = true;
     for (int k = g; k < ns; k += G) {
         const ThermoRec t = record(k);
         const double gk = gibbs(t);
-        odd |= !(gk >= G_MIN && gk <= G_MAX);
+        odd |= !(fabs(gk) <= G_FAR);
+        calm &= fabs(gk) <= G_CALM;
         const double e = fexp(gk);
         at_(k, F_E) = e;
         const double cp = t.c[0] + T * (t.c[1] + T * (t.c[2] + T * (t.c[3] + T * t.c[4])));
@@ -194,25 +195,31 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
         pw[6 * S + s] = ix * ix * ix;
     }
     {
-        const int f = __ballot(odd) ? 1 : 0;
-        if (lane == 0) ints[wave] = f;
+        const uint64_t f = __ballot(odd), c = __ballot(!calm);
+        if (lane == 0) {
+            masks[2 * wave] = f;
+            masks[2 * wave + 1] = c;
+        }
     }
     __syncthreads();
-    int flags = 0;
-    for (int w = 0; w < nwave; ++w) flags |= ints[w];
-    const bool logs = __builtin_amdgcn_readfirstlane(flags);
+    uint64_t mask = 0, wild = 0;
+    for (int w = 0; w < nwave; ++w) {
+        mask |= masks[2 * w];
+        wild |= masks[2 * w + 1];
+    }
+    const bool far = (mask >> lane) & 1;       // this state's reactions take the exponential of the sum
+    // every state's products of exponentials are in range
+    const bool quiet = __builtin_amdgcn_readfirstlane((int)(wild | wild >> 32)) == 0;
     if (tid < S) {
         // n_Ns = P V / (R T) - RN(sum of the others)
         dd a{0.0, 0.0};
         for (int q = 0; q < G; ++q) a = dd_add(a, dd{part(2 * q), part(2 * q + 1)});
         at_(bath, F_C) = ((P * Vv) / (RU * T) - a.hi) / Vv;
     }
-    double lnP = 0.0;
-    if (logs) {
-        // some g out of range: exponentials of the sums, from g itself
+    if (far) {
+        // g itself in place of its exponential
         for (int k = g; k < ns; k += G) at_(k, F_E) = gibbs(record(k));
         if (tid < S) at_(ns, F_E) = 0.0;
-        lnP = log(PREF / (RU * T));
     }
     __syncthreads();
 
@@ -304,41 +311,63 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
     // the elementary part of two reactions, without branches: the chain of one
     // exponential fills the gaps of the other's
     typedef double V2 __attribute__((ext_vector_type(2)));
-    auto rates = [&](const Rxn& r0, const Rxn& r1, V2& lnkf, V2& q) {
+    auto ratio = [&](const Rxn& r, bool& ok) {      // kr / kf
+        const double f = r.x[0] * r.x[1] * r.x[2], b = r.x[3] * r.x[4] * r.x[5];
+        const double bp = b * r.pw, kq = bp * reciprocal(f);
+        ok = true;
+        if (!quiet)
+            ok = normal(r.x[0] * r.x[1]) && normal(f) && normal(r.x[3] * r.x[4]) && normal(b) && normal(bp) && normal(kq);
+        return kq;
+    };
+    auto rates = [&](const Rxn& r0, const Rxn& r1, V2& lnkf, V2& q, bool& ok0, bool& ok1) {
         auto both = [&](auto f) { return V2{f(r0), f(r1)}; };
         lnkf = both([&](const Rxn& r) { return r.lnA + r.b * lnT - r.th * invT; });
         const V2 kf = vmap(lnkf, [](double x) { return fexp_in(x); });
         const V2 Pf = both([](const Rxn& r) { return r.c[0] * r.c[1] * r.c[2]; });
         const V2 Pb = both([](const Rxn& r) { return r.w & GI_REV ? r.c[3] * r.c[4] * r.c[5] : 0.0; });
         // (an irreversible reaction's is 0: its product may overflow with k_f, and inf * 0 is NaN)
-        const V2 kq = both([](const Rxn& r) {
-            return r.w & GI_REV ? (r.x[3] * r.x[4] * r.x[5]) * reciprocal(r.x[0] * r.x[1] * r.x[2]) * r.pw : 0.0;
-        });
+        V2 kq = {ratio(r0, ok0), ratio(r1, ok1)};
+        if (!(r0.w & GI_REV)) kq[0] = 0.0, ok0 = true;
+        if (!(r1.w & GI_REV)) kq[1] = 0.0, ok1 = true;
         q = kf * Pf - (kf * kq) * Pb;
     };
-    auto rate = [&](const Rxn& r, uint32_t rec, const Extra& ex, int l, double lnkf, double q) {
+    auto rate = [&](const Rxn& r, uint32_t rec, const Extra& ex, int l, double lnkf, double q, bool ok) {
         const uint32_t w = r.w;
         const int kind = w & 7;
-        // what the two together leave out: tabulated rates, exponents near the end
-        // of the range, reverse rates from the sum of the exponents
-        if (__builtin_expect(logs || __any(!(fabs(lnkf) < -LNK_MIN)) || (EXT && kind_table(kind)), false)) {
-            if (EXT && kind_table(kind)) {
-                DevMech td{};
-                td.tab = gm->tab;
-                td.tabd = gm->tabd;
-                double a, b;
-                lnkf += table_lnk(td, kind, (int)(word(rec, l + 7) & 0xFFFF), T, invT, lnT, P, a, b);
-            }
-            double dG = 0.0;
-            if (logs) {
+        const double Pf = r.c[0] * r.c[1] * r.c[2], Pb = r.c[3] * r.c[4] * r.c[5];
+        if (EXT && kind_table(kind)) {
+            DevMech td{};
+            td.tab = gm->tab;
+            td.tabd = gm->tabd;
+            double a, b;
+            lnkf += table_lnk(td, kind, (int)(word(rec, l + 7) & 0xFFFF), T, invT, lnT, P, a, b);
+            const double kf = fexp(lnkf);
+            q = kf * Pf;
+            if (w & GI_REV) q -= kf * ratio(r, ok) * Pb;
+        }
+        // states where the two together could not hold the factors
+        const bool bad = far || !ok || !(fabs(lnkf) < LNK_FAR);
+        if (__builtin_expect(__any(bad), false)) {
+            double y = fexp(lnkf) * Pf;
+            if (w & GI_REV) {
+                double x = lnkf, mf = 1.0, mb = r.pw;
+                int e = 0;
+                if (far) {
+                    x -= (double)((int)((w >> 8) & 7) - 3) * log(PREF / (RU * T));
+                    mb = 1.0;
+                }
 #pragma unroll
-                for (int a = 0; a < NSLOT; ++a) dG += a < MAXSIDE ? -r.x[a] : r.x[a];
-                dG -= (double)((int)((w >> 8) & 7) - 3) * lnP;
-            } else {
-                dG = log((r.x[3] * r.x[4] * r.x[5]) / (r.x[0] * r.x[1] * r.x[2]) * r.pw);
+                for (int a = 0; a < NSLOT; ++a) {
+                    if (far) {
+                        x += a < MAXSIDE ? -r.x[a] : r.x[a];
+                    } else {
+                        (a < MAXSIDE ? mf : mb) *= __builtin_amdgcn_frexp_mant(r.x[a]);
+                        e += a < MAXSIDE ? -__builtin_amdgcn_frexp_exp(r.x[a]) : __builtin_amdgcn_frexp_exp(r.x[a]);
+                    }
+                }
+                y -= scaled_exp(x, mb / mf, e) * Pb;
             }
-            q = fexp(lnkf) * (r.c[0] * r.c[1] * r.c[2]);
-            if (w & GI_REV) q -= fexp(lnkf + dG) * (r.c[3] * r.c[4] * r.c[5]);
+            q = bad ? y : q;
         }
         if (kind != K_ELEM && !kind_table(kind)) {
             double M = Ctot;      // + sum (alpha_k - 1) [C]_k
@@ -415,9 +444,10 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
                 const Rxn r0 = read(rec, ex, l), r1 = read(rec, ex, l + 16);
                 PJ_READS_FIRST();
                 V2 lnkf, q;
-                rates(r0, r1, lnkf, q);
-                q[0] = rate(r0, rec, ex, l, lnkf[0], q[0]);
-                q[1] = rate(r1, rec, ex, l + 16, lnkf[1], q[1]);
+                bool ok0, ok1;
+                rates(r0, r1, lnkf, q, ok0, ok1);
+                q[0] = rate(r0, rec, ex, l, lnkf[0], q[0], ok0);
+                q[1] = rate(r1, rec, ex, l + 16, lnkf[1], q[1], ok1);
                 // the stage before has been added by all
                 if (t == 0 && l == 0) __syncthreads();
                 part(wave + nwave * (4 * t + (l >> 4))) = q[0];

@@ -68,3 +68,86 @@ def test_irreversible_reaction_beside_an_overflowing_equilibrium(torch_cuda, api
     check_source(api.eval_source(mech, xs, ps, "conp", "C").cpu().numpy(), f_o, f_b, f"source terms {shape}")
     J = api.sparse_to_dense(mech, api.eval_jacobian_sparse(mech, xs, ps, "conp", "C").cpu().numpy(), "C")
     check_jac(J, J_o, J_b, f"sparse Jacobian {shape}")
+
+
+SHAPES = [(64, 2), (64, 8), (1, 2), (1, 4), (2, 2), (2, 4), (4, 1)]
+
+
+@pytest.mark.parametrize("shape", SHAPES)
+@pytest.mark.parametrize("form", ["conp", "conv"])
+@pytest.mark.parametrize("low,high", [
+    # three molecules a side whose exponentials together underflow (e^-1005) or
+    # overflow (e^+990), none alone; the reactions are near equilibrium
+    (-340.0, 334.0),
+    # two together, or one alone, out of range
+    (-420.0, 380.0), (-760.0, 740.0),
+    # beside the bounds of the product: three are e^-645 and e^+630, e^-210 ...
+    (-217.0, 214.0), (-70.0, 60.0),
+])
+def test_equilibria_at_the_ends_of_the_range(torch_cuda, api, tmp_path, low, high, form, shape):
+    torch = torch_cuda
+    E = lambda a, b, lnA, b_, th, **kw: synth.Reaction(kw.pop("type", "ELEM"), True, a, b, lnA, b_, th, **kw)  # noqa: E731
+    rx = [E([(0, 2), (1, 1)], [(2, 2), (3, 1)], 3.0, 0.0, 1500.0), E([(4, 1), (5, 2)], [(6, 1), (7, 2)], 4.0, 0.3, 2000.0),
+          E([(0, 1), (4, 1)], [(2, 1), (6, 1)], 8.0, 0.0, 500.0),
+          E([(1, 1)], [(3, 1)], 6.0, 0.0, 500.0, type="THREEBODY", eff=[(2, 3.0), (8, 0.5)]),
+          E([(5, 1)], [(7, 1)], 9.0, 0.0, 700.0, type="LINDEMANN", low=(12.0, 0.0, 300.0)),
+          # k_f itself below the range, e^-900; far from equilibrium, but no rate of note
+          E([(4, 1)], [(6, 1)], 5.0, 0.0, 905.0e3)]
+    m, path = isomers([low, low + 3, low + 5, low + 4, high, high - 4, high - 6, high - 5, -20.0], rx, tmp_path, "ends")
+    n = 70
+    T = np.linspace(985.0, 1015.0, n)
+    x, p = isomer_states(9, n, T)
+    if form == "conv":
+        x[:, 1], p = p.copy(), np.ones(n)
+    o = oracle.Oracle(path)
+    f_o, f_b = o.source(x, p, form, bound=True)
+    J_o, J_b = o.jacobian(x, p, form, bound=True)
+    assert np.isfinite(f_o).all() and np.isfinite(J_o).all()
+    xs, ps = torch.from_numpy(x).cuda(), torch.from_numpy(p).cuda()
+    mech = api.load_mechanism(path)
+    mech.set_launch(*shape)
+    check_source(api.eval_source(mech, xs, ps, form, "C").cpu().numpy(), f_o, f_b, f"source terms {shape}")
+    J = api.sparse_to_dense(mech, api.eval_jacobian_sparse(mech, xs, ps, form, "C").cpu().numpy(), "C")
+    check_jac(J, J_o, J_b, f"sparse Jacobian {shape}")
+    if shape[0] <= 4:
+        v = np.random.default_rng(1).standard_normal(x.shape)
+        j_o, _, j_b, _ = o.adjoint(x, p, v, form, bound=True)
+        j, _ = api.eval_adjoint(mech, xs, ps, torch.from_numpy(v).cuda(), form, "C")
+        check_jac(j.cpu().numpy(), j_o, j_b, f"J^T v {shape}")
+
+
+@pytest.mark.parametrize("shape", [(0, 0)] + SHAPES)
+@pytest.mark.parametrize("name,n", [("ns13", 131), ("ns53", 131), ("ns111x", 131)])
+@pytest.mark.parametrize("odd", ["cold", "absent", "nan"])
+def test_results_do_not_depend_on_the_neighbours(torch_cuda, api, name, n, odd, shape, mech_dir):
+    """Every third state replaced by one that takes other paths (60 K, where every
+    equilibrium is out of range; half the species absent; no number): the others
+    keep their bits."""
+    from conftest import workload_file
+    torch = torch_cuda
+    m, path = workload_file(name, mech_dir)
+    x, p = synth.pack_state(synth.make_states(m, n, 3), "conp", "C")
+    y = x.copy()
+    rows = np.arange(1, n, 3)
+    if odd == "cold":
+        y[rows, 0] = 60.0
+    elif odd == "absent":
+        y[rows, 2:] *= np.random.default_rng(1).random((len(rows), m.n_species - 1)) < 0.5
+    else:
+        y[rows, 0] = np.nan
+    keep = torch.from_numpy(np.setdiff1d(np.arange(n), rows)).cuda()
+    mech = api.load_mechanism(path)
+    mech.set_launch(*shape)
+    if shape[0] == 4:
+        assert mech.kernel("sparse", "C", n)[0] == "scatter"
+    ps, v = torch.from_numpy(p).cuda(), torch.from_numpy(np.random.default_rng(2).standard_normal(x.shape)).cuda()
+    got = []
+    for z in (x, y):
+        zs = torch.from_numpy(z).cuda()
+        got.append([api.eval_source(mech, zs, ps, "conp", "C")[keep], api.eval_jacobian_sparse(mech, zs, ps, "conp", "C")[keep],
+                    api.eval_adjoint(mech, zs, ps, v, "conp", "C", with_grad=False)[0][keep]])
+    one_wave = shape[1] == 1
+    for what, a, b in zip(("source", "sparse", "adjoint"), *got):
+        # (several waves of the scatter kernels add in any order)
+        if one_wave or mech.kernel(what, "C", n)[0] != "scatter":
+            assert torch.equal(a, b), what
