@@ -624,7 +624,11 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             // PLAIN: every reaction of the chunk is elementary (c = 1)
             auto react = [&](auto plain) {
             constexpr bool PLAIN = decltype(plain)::value;
-            V lnkf = lnA + bexp * lnT - th * invT;
+            // (written as multiply-adds: th invT has other uses, and a rounding of
+            // its own would show in k_f)
+            V lnkf;
+#pragma unroll
+            for (int v = 0; v < RN; ++v) lnkf[v] = fma(-th, invT[v], fma(bexp, lnT[v], lnA));
             V dlkt_dT = 0.0, dlkt_dP = 0.0;
             if (EXT && !PLAIN && (cm & CHUNK_TAB) && kind_table(kind)) {
                 DevMech td{};

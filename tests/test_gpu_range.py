@@ -151,3 +151,40 @@ def test_results_do_not_depend_on_the_neighbours(torch_cuda, api, name, n, odd, 
         # (several waves of the scatter kernels add in any order)
         if one_wave or mech.kernel(what, "C", n)[0] != "scatter":
             assert torch.equal(a, b), what
+
+
+@pytest.mark.parametrize("shapes", [((1, 4), (2, 4), (64, 4))])
+@pytest.mark.parametrize("name,n", [("ns53", 600), ("ns111", 200)])
+@pytest.mark.parametrize("T_range", [(600.0, 2200.0), (300.0, 700.0)])
+def test_rounding_is_no_larger_than_the_scatter_kernels(torch_cuda, api, name, n, T_range, shapes, mech_dir):
+    """Errors against the oracle in long double, over the running error bound of
+    each value: their root mean square and 99th percentile against the scatter
+    kernels' of the same states.  Both are sums over tens of thousands of
+    values, to 3 % of each other (a further rounding of ln k_f: 6 % and 11 %)."""
+    from conftest import workload_file
+    torch = torch_cuda
+    m, path = workload_file(name, mech_dir)
+    x, p = synth.pack_state(synth.make_states(m, n, 17, T_range=T_range), "conp", "C")
+    o = oracle.Oracle(path)
+    k = n // 8
+    f_l, (_, f_b) = o.source_ld(x, p), o.source(x, p, "conp", bound=True)
+    J_l, (_, J_b) = o.jacobian_ld(x[:k], p[:k]), o.jacobian(x[:k], p[:k], "conp", bound=True)
+    xs, ps = torch.from_numpy(x).cuda(), torch.from_numpy(p).cuda()
+    mech = api.load_mechanism(path)
+    on = mech.pattern_dense()
+    on[:2] = False
+
+    def errors(shape):
+        mech.set_launch(*shape)
+        f = api.eval_source(mech, xs, ps, "conp", "C").cpu().numpy()
+        J = api.sparse_to_dense(mech, api.eval_jacobian_sparse(mech, xs[:k], ps[:k], "conp", "C").cpu().numpy(), "C")
+        got = []
+        for a, l, b in ((f, f_l, f_b), (J[:, on], J_l[:, on], J_b[:, on])):
+            r = (np.abs(a - l) / np.maximum(b, 1e-300))[b > 0]
+            got += [np.sqrt((r * r).mean()), np.quantile(r, 0.99)]
+        return np.array(got)
+    ref = errors((4, 1))
+    for shape in shapes:
+        e = errors(shape)
+        print(name, T_range, shape, e / ref, flush=True)
+        assert (e <= 1.03 * ref).all(), (shape, e / ref)
