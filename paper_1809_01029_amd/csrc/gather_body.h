@@ -30,7 +30,8 @@
 // per species in place of one per reaction.  A reaction whose product leaves the
 // range of normal numbers, or whose kf would, takes the product of the mantissas
 // and the sum of the exponents instead (scaled_exp); a state with a |g_k| above
-// 700, whose exponential alone is out of range, the exponential of the sum.  Either
+// 350 (a carbon atom below 240 K), of which two exponentials together need not be
+// in range, the exponential of the sum.  Either
 // is decided for each state by itself: its results don't depend on its neighbours.
 //
 // A workgroup evaluates NV states, NV compile-time; every lane works for all
@@ -81,8 +82,8 @@ enum { SC_LNT = 0, SC_NSUM, SC_CB, SC_ICB, SC_DP, SC_DDP, SC_TT, SC_TS, SC_ST, S
 // Jacobian, whose lists read single fields, an array each (8.65 ms against 9.28).
 enum { A_E = 0, A_C = 1, A_I = 2, A_H = 3, A_CP = 4, A_Y = 5, A_VV = 6, A_W = 0, A_IC = 1, A_VT = 2 };
 constexpr double C_TINY = 1e-150;
-// |g| up to which one exponential is a normal number, and six together are
-constexpr double G_FAR = 700.0, G_CALM = 115.0;
+// |g| up to which two exponentials together are a normal number, and six are
+constexpr double G_FAR = 350.0, G_CALM = 115.0;
 constexpr double LNK_FAR = 690.0;
 __device__ inline bool normal(double x) { return __builtin_amdgcn_class(x, 0x108); }
 
@@ -396,7 +397,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
 
     // ---- (1) closure (wave 0), thermodynamics (the others; with one wave all)
     const int tb = nwave > 1 ? 64 : 0;
-    bool odd_c = false, wild_g = false;
+    bool odd_c = false;
     int far_g = 0;                               // by state
     // (a state past the end computes a copy of the last)
     auto clamp_state = [&](int v) { const long q = qg * NV + v; return q < n ? q : n - 1; };
@@ -514,7 +515,6 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             const double h = a0 + T * (a(5) + T * (a(6) + T * (a(7) + T * a(8)))) + a(12) * invT;
             const double sr = a0 * lnT + T * (a1 + T * (a(9) + T * (a(10) + T * a(11)))) + a(13);
             const double g = h - sr;
-            wild_g |= !(fabs(g) <= G_CALM);
             if (!(fabs(g) <= G_FAR)) far_g |= 1 << v;
             if (logs) {
                 A[fld(k, A_E) * NV + v] = g;
@@ -531,7 +531,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     };
     if (tid >= tb) thermo(0);
     {
-        int f = (__ballot(odd_c) ? 1 << NV : 0) | (__ballot(wild_g) ? 2 << NV : 0);
+        int f = __ballot(odd_c) ? 1 << NV : 0;
 #pragma unroll
         for (int v = 0; v < NV; ++v) f |= __ballot((far_g >> v) & 1) ? 1 << v : 0;
         if (lane == 0) ints[wave] = f;
@@ -541,7 +541,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     for (int w = 0; w < nwave; ++w) flags |= ints[w];
     flags = __builtin_amdgcn_readfirstlane(flags);
     const int logs = flags & ((1 << NV) - 1);       // states whose reactions take the exponential of the sum
-    const bool tiny = (flags >> NV) & 1, calm = !((flags >> NV) & 2);
+    const bool tiny = flags >> NV;
     if (logs) {
         // g itself in place of its exponential
         if (tid >= tb) thermo(logs);
@@ -644,7 +644,9 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             }
             // slots: concentration products, ratio kr / kf, dH
             V Pf = 1.0, Pb = 1.0, kq = 1.0, dH = 0.0, Pft = 1.0, Pbt = 1.0, lam = 0.0, dcp = 0.0, dvv = 0.0;
-            bool fits[RN];       // the product of the exponentials is precise
+            // the product of the exponentials is precise: every step normal (tested always:
+            // a branch round the test costs more)
+            bool fits[RN];
 #pragma unroll
             for (int v = 0; v < RN; ++v) fits[v] = true;
             {
@@ -665,11 +667,9 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 Pb = xs[3][0] * xs[4][0] * xs[5][0];
                 const V k0 = xs[0][1] * xs[3][1], k1 = xs[1][1] * xs[4][1], k2 = xs[2][1] * xs[5][1], k01 = k0 * k1;
                 kq = k01 * k2 * vec(PW, (w >> 8) & 7);
-                if (!calm)
 #pragma unroll
                     for (int v = 0; v < RN; ++v)
-                        fits[v] = normal(k0[v]) && normal(k1[v]) && normal(k2[v]) && normal(k01[v]) && normal((k01 * k2)[v]) &&
-                                  normal(kq[v]);
+                        fits[v] = normal(k01[v]) && normal((k01 * k2)[v]) && normal(kq[v]);
                 if (DER) dH = ((xs[3][2] - xs[0][2]) + (xs[4][2] - xs[1][2])) + (xs[5][2] - xs[2][2]);
                 if (DER && tiny) {
                     // absent species at 1e-150
@@ -707,7 +707,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
                 bad[v] = rev && (!fits[v] || far(v) || !(fabs(lnkf[v]) < LNK_FAR));
                 some |= bad[v];
             }
-            if (__any(some)) {
+            if (__builtin_expect(__any(some), false)) {
 #pragma unroll
                 for (int v = 0; v < RN; ++v) {
                     double x = lnkf[v], m = vec(PW, (w >> 8) & 7)[v];

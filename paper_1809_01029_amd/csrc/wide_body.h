@@ -10,7 +10,7 @@
 //
 //   C_k, exp(g_k)
 //
-// (the latter g_k in a state where one exceeds 700), and the
+// (the latter g_k in a state where one exceeds 350), and the
 // rates of progress of the reactions that the waves evaluate between two
 // barriers; enthalpies are evaluated again at the end rather than kept.
 //
@@ -316,7 +316,7 @@ pj_wide_source(const GatherMech* const gmp, const long n, const long g0, const l
         const double bp = b * r.pw, kq = bp * reciprocal(f);
         ok = true;
         if (!quiet)
-            ok = normal(r.x[0] * r.x[1]) && normal(f) && normal(r.x[3] * r.x[4]) && normal(b) && normal(bp) && normal(kq);
+            ok = normal(f) && normal(b) && normal(bp) && normal(kq);
         return kq;
     };
     auto rates = [&](const Rxn& r0, const Rxn& r1, V2& lnkf, V2& q, bool& ok0, bool& ok1) {
