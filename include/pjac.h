@@ -248,7 +248,8 @@ pj_status pj_mech_get_arrhenius(const pj_mech* mech, double* lnA, double* b, dou
  * the LDS of one workgroup, and enough waves for about 8 resident waves per compute unit.  A
  * states_per_group that does not fit for a mode is ignored for that mode.
  * One or two states with at least 2 waves (a multiple of the states, and for
- * Jacobians one for every 320 reactions of a state) run kernels that add in a
+ * Jacobians one for every 320 reactions of a state, for adjoints one
+ * for every 640 and for source terms one for every 768 reactions) run kernels that add in a
  * fixed order, without atomics, unless the mechanism was loaded for the
  * run-time slot search or the fixed-order additions.  So does the adjoint with
  * one state (without fused source terms); its parameter sums are added over

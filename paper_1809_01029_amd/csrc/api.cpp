@@ -51,7 +51,10 @@ static int gather_mode(int mode) { return mode == MODE_SRC ? GM_SRC : mode == MO
 // A call with S states and w waves per workgroup runs on the gather kernels
 // (gather_body.h) if they are built for it: at most two states (the adjoint
 // one), each with a wave of its own or more, a wave's reactions in at most GATHER_BLOCKS blocks
-// of 64.  One wave per workgroup stays with the scatter kernels (their fixed
+// of 64 (adjoints in 2 GATHER_BLOCKS, source terms in 12: with more the scatter
+// kernels are the faster; 360 species, 34 blocks, 6410 states, scatter -> gather, us:
+// source terms 2x2 184 -> 285, 1x3 205 -> 180; adjoint 1x2 1090 -> 1370, 1x4
+// 907 -> 803).  One wave per workgroup stays with the scatter kernels (their fixed
 // order is documented), and so do the run-time slot search and the fixed-order
 // option, whose results are theirs by definition.  A dense Jacobian in layout
 // F is written by columns of single states at S = 1: 2993 us against the
@@ -61,7 +64,8 @@ static bool gather_takes(const Mechanism& m, int mode, pj_layout layout, int64_t
     if (!m.gm.ok || m.dm.lsearch || m.dm.det) return false;
     if (S > (mode == MODE_ADJ ? 1 : 2) || w < 2 || w % S) return false;
     if (mode == MODE_DENSE && layout == PJ_LAYOUT_F && S == 1) return false;
-    if ((mode == MODE_SPARSE || mode == MODE_DENSE) && (m.nr + 63) / 64 > GATHER_BLOCKS * (w / S)) return false;
+    const int most = mode == MODE_SRC ? 12 * w : mode == MODE_ADJ ? 2 * GATHER_BLOCKS * w : GATHER_BLOCKS * (w / S);
+    if ((m.nr + 63) / 64 > most) return false;
     if ((n / S + 8) * 64 * w >= (int64_t)1 << 32) return false;
     return gather_lds(m.gm, gather_mode(mode), S) <= m.lds_max;
 }

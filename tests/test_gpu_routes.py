@@ -2,6 +2,8 @@
 choice, and the results of both: the route is asserted, so that a case cannot
 slip to the other side of its line, and sampled states (the first, the last and
 some between) are compared with the oracle under ``oracle.gates``."""
+import os
+
 import numpy as np
 import pytest
 
@@ -152,3 +154,51 @@ def test_automatic_source_terms_are_reproducible(torch_cuda, api, name, n, layou
         if sg.mech.kernel("source", layout, n)[0] == "wide":
             a, b = (api.eval_source(sg.mech, sg.xs, sg.ps, "conp", layout) for _ in range(2))
             assert torch.equal(a, b)
+
+
+def described(name, mech_dir):
+    """(mechanism, path): a workload, or genN, N species with 6.5 N reactions."""
+    if not name.startswith("gen"):
+        return workload_file(name, mech_dir)
+    ns = int(name[3:])
+    m = synth.make_mechanism(ns, 13 * ns // 2, ns)
+    return m, synth.write_mechanism(m, os.path.join(str(mech_dir), name + ".pjm"))
+
+
+@pytest.mark.parametrize("name,shape,mode,layout,n,want", [
+    # set shapes (states, waves): reactions a wave takes, 360 species = 34 blocks of 64
+    ("ns360", (2, 2), "source", "C", 6410, ("scatter", 2, 2)),
+    ("ns360", (1, 3), "source", "C", 6410, ("gather", 1, 3)),
+    ("ns360", (1, 2), "adjoint", "C", 6410, ("scatter", 1, 2)),
+    ("ns360", (1, 4), "adjoint", "C", 6410, ("gather", 1, 4)),
+])
+def test_kernel_choice(torch_cuda, api, name, shape, mode, layout, n, want, mech_dir):
+    """Both sides of a line: the route, and the results of the path that it takes."""
+    torch = torch_cuda
+    m, path = described(name, mech_dir)
+    mech = api.load_mechanism(path)
+    if shape:
+        mech.set_launch(*shape)
+    assert mech.kernel(mode, layout, n) == want
+    x, p = synth.pack_state(synth.make_states(m, n, 4), "conp", "C")
+    dev = lambda a: torch.from_numpy(np.ascontiguousarray(a if layout == "C" else a.T)).cuda()  # noqa: E731
+    xs, ps = dev(x), torch.from_numpy(p.copy()).cuda()
+    idx = sample(n)
+    ti = torch.from_numpy(idx).cuda()
+    pick = lambda t: (t[ti] if layout == "C" else t[..., ti].movedim(-1, 0)).cpu().numpy()  # noqa: E731
+    o = oracle.Oracle(path)
+    what = f"{name} {mode} {layout} {n}"
+    if mode == "source":
+        f_o, f_b = o.source(x[idx], p[idx], "conp", bound=True)
+        check_source(pick(api.eval_source(mech, xs, ps, "conp", layout)), f_o, f_b, what)
+    elif mode == "adjoint":
+        v = np.random.default_rng(4).standard_normal(x.shape)
+        j_o, _, j_b, _ = o.adjoint(x[idx], p[idx], v[idx], "conp", bound=True)
+        check_jac(pick(api.eval_adjoint(mech, xs, ps, dev(v), "conp", layout)[0]), j_o, j_b, what)
+    else:
+        J_o, J_b = o.jacobian(x[idx], p[idx], "conp", bound=True)
+        if mode == "sparse":
+            J = api.sparse_to_dense(mech, pick(api.eval_jacobian_sparse(mech, xs, ps, "conp", layout)), "C")
+        else:
+            J = api.dense_as_sij(api.eval_jacobian_dense(mech, xs, ps, "conp", layout), layout)[ti].cpu().numpy()
+        check_jac(J, J_o, J_b, what)
