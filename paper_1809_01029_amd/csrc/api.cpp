@@ -76,26 +76,32 @@ static bool wide_takes(const Mechanism& m, int mode, int S, int w) {
     return mode == MODE_SRC && m.gm.ok && !m.dm.det && S == 64 && w >= 2 && wide_fits(m.gm, w);
 }
 
-// The automatic choice of the wide kernel.  Measured on MI355X, scatter (4
-// states and one wave a workgroup) -> wide, us per call: 13 species, 16384
-// states 19 -> 12, 262144 states 214 -> 77; 20 species 497 -> 214; 53 species,
-// 16384 states 76 -> 43, 262144 states 922 -> 599; 8192 states, half the chip's
-// compute units: 42 -> 40, 13 species 11 -> 11.
+// The automatic choice of the wide kernel: two workgroups of 8 waves a compute
+// unit (about 54 species; of 70, 131072 states 563 us against the gather kernels'
+// 554), more than 8192 states.  A workgroup's time is nearly the same however many
+// share its compute unit, so what counts is how full the last round of workgroups
+// over the 256 compute units is: 53 species, 16390 states (1.002 rounds, two
+// workgroups on some units) 94 us against 67 (gather), 26000 95 against 99, 33000
+// 140 against 122, 40000 141 against 147, 65536 (four rounds) 179 against 237;
+// 32 species (scatter) 24001 states 63 against 59, 26000 63 against 68, 36000
+// 92 against 83, 40000 92 against 94.
 static bool wide_choice(const Mechanism& m, int mode, int64_t n, int& S, int& w) {
-    if (mode != MODE_SRC || n <= 8192) return false;
-    // the waves that fill a compute unit best, the fewest of equals; while the
-    // chip isn't full, many
-    int best = 0;
-    for (int v = 2; v <= 8; v *= 2) {
-        if (!wide_takes(m, mode, 64, v)) continue;
-        const int waves = n <= 16384 ? (v == (m.nr > 64 ? 8 : 4) ? 2 : 1)
-                                     : (int)std::min<int64_t>(16, m.lds_max / wide_lds(m.gm, v) * (2 * v));
-        if (waves <= best) continue;
-        best = waves;
-        S = 64;
-        w = v;
-    }
-    return best > 0;
+    if (mode != MODE_SRC || n <= 8192 || !wide_takes(m, mode, 64, 4) || 2 * wide_lds(m.gm, 4) > m.lds_max) return false;
+    const int blocks = (m.nr + 63) / 64;
+    const int64_t round = 256 * 64, rounds = (n + round - 1) / round;
+    const bool four = wide_takes(m, mode, 64, 2) && 4 * wide_lds(m.gm, 2) <= m.lds_max;     // of 4 waves
+    // One round: the gather kernels up to 13000 states of more than 256 reactions,
+    // the scatter kernels up to 12288 of 129 to 256 where their grid is a multiple of
+    // 8 (only then do they map neighbouring workgroups to one XCD): 32 species, 12000
+    // states 31 against 38 us, 36 species 38 against 40, but 12001 39 against 38 and
+    // 47 against 40.
+    if (rounds == 1 && blocks >= 3 && blocks <= 4 && n <= 12288 && (n + 3) / 4 % 8 == 0) return false;
+    if (rounds == 1 ? blocks > 4 && n <= 13000 : rounds < 4 && blocks > 1 && 5 * n < 4 * rounds * round && !(rounds == 3 && four))
+        return false;
+    // while each workgroup has a compute unit of its own, many waves
+    S = 64;
+    w = rounds == 1 ? (blocks > 1 && wide_takes(m, mode, 64, 8) ? 8 : 4) : four ? 2 : 4;
+    return true;
 }
 
 // The automatic choice between the gather and the scatter kernels for a call
@@ -135,12 +141,15 @@ static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_
         return gather_lds(m.gm, GM_ADJ, 1) * (12 / v) <= m.lds_max && take(1, v);
     }
     if (mode == MODE_SRC) {
-        // the wide kernel's LDS holds about 75 species; of more, scatter -> gather:
+        // 20 species, 4096 states 19 -> 14, 8192 23 -> 27; 40 species, 6001 states
+        // 49 -> 27, 8192 33 -> 34; 53 species, 12001 states 64 -> 51, 24001 93 -> 91;
         // 80 species, 262144 states 1410 -> 1220, 111 species 2430 -> 1723, 360
-        // species, 65536 states 5413 -> 1563
+        // species, 65536 states 5413 -> 1563.  32 species, 20000 states: 52 -> 62.
         if (n <= 1024) return take(1, 4);
-        if (!(n <= 4096 && blocks >= 2) && !(n <= 8192 && blocks >= 5) && wide_takes(m, mode, 64, 8)) return false;
-        return blocks >= 2 && take(2, blocks <= 9 ? 2 : 4);
+        int s, v;
+        if (blocks < 2 || wide_choice(m, mode, n, s, v)) return false;
+        if (n > 4096 && blocks <= 4) return false;
+        return take(2, blocks <= 9 ? 2 : 4);
     }
     if (!few && blocks <= 4) return false;
     // layout F: two states write twice as long runs; one if two leave a compute

@@ -171,6 +171,21 @@ def described(name, mech_dir):
     ("ns360", (1, 3), "source", "C", 6410, ("gather", 1, 3)),
     ("ns360", (1, 2), "adjoint", "C", 6410, ("scatter", 1, 2)),
     ("ns360", (1, 4), "adjoint", "C", 6410, ("gather", 1, 4)),
+
+    # source terms: few states; more than two wide workgroups a compute unit; the
+    # last round of 256 x 64 states at least 80 % full; scatter grids of a multiple of 8
+    ("gen20", None, "source", "C", 4096, ("gather", 2, 2)),
+    ("gen20", None, "source", "C", 4097, ("scatter", 4, 1)),
+    ("ns53", None, "source", "C", 13000, ("gather", 2, 2)),
+    ("ns53", None, "source", "C", 13001, ("wide", 64, 8)),
+    ("ns53", None, "source", "C", 16384, ("wide", 64, 8)),
+    ("ns53", None, "source", "C", 16385, ("gather", 2, 2)),
+    ("ns53", None, "source", "F", 26214, ("gather", 2, 2)),
+    ("ns53", None, "source", "F", 26215, ("wide", 64, 4)),
+    ("ns53", None, "source", "C", 49153, ("wide", 64, 4)),
+    ("gen32", None, "source", "C", 12000, ("scatter", 4, 1)),
+    ("gen32", None, "source", "C", 12001, ("wide", 64, 8)),
+    ("ns111", None, "source", "C", 20000, ("gather", 2, 4)),
 ])
 def test_kernel_choice(torch_cuda, api, name, shape, mode, layout, n, want, mech_dir):
     """Both sides of a line: the route, and the results of the path that it takes."""
