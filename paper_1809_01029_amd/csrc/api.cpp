@@ -115,7 +115,7 @@ static bool wide_choice(const Mechanism& m, int mode, int64_t n, int& S, int& w)
 //     1388 -> 1110, dense (17799) 408 -> 375; 111 species, 16232 states 752 -> 620
 //     (F 805 -> 716); 360 species, 4096 states 767 -> 660 (F 1270 -> 848)
 //   fewer: 20 species, 131072 states, sparse 996 -> 1159
-static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_t n, int& S, int& w) {
+static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool grad, int& S, int& w) {
     const int blocks = (m.nr + 63) / 64;
     const bool few = n <= 2048;
     auto take = [&](int s, int v) {
@@ -125,19 +125,25 @@ static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_
         return true;
     };
     if (mode == MODE_ADJ) {
-        // Few states: a workgroup each.  Then the workgroups' additions of their
+        // Few states: a workgroup each (256: 53 species 51 -> 46, but 13 species 19.0
+        // -> 21.1 and 220 species 70 -> 80).  Then the workgroups' additions of their
         // parameter sums to the output weigh (about 50 ps each, 256 of four
-        // states send a quarter of them): 111 species, 1024 states 77 -> 82,
-        // 4096 states 208 -> 179.  A wave holds 168 registers, a compute unit 12
+        // states send a quarter of them): 111 species, 1024 states 88 -> 120,
+        // 4096 states 208 -> 178; 220 species (4 states a
+        // workgroup), 512 states 86 -> 93, 1000 143 -> 114, 360 species (2) 256 86 -> 91, 512
+        // 123 -> 111.
+        // A wave holds 168 registers, a compute unit 12
         // waves: taken where the LDS lets in workgroups for all 12, or where a
-        // state needs 8 waves (360 species, 8192 states 1000 -> 650).  53 species,
-        // 65536 states 1047 -> 779 (2 waves; 3: 849), 111 species, 54054 states
+        // state needs 8 waves (360 species, 8192 states 962 -> 640).  53 species,
+        // 4096 states 161 -> 138 (4 waves; 2: 200), 16384 383 -> 297 (2: 303), without
+        // a gradient 12000 143 -> 127 (2 waves; 4: 172),
+        // 65536 1047 -> 779 (2 waves; 3: 849), 111 species, 54054 states
         // 1492 -> 1229 (4 waves; 3: 1744); 160 species, two workgroups:
         // 1319 -> 1654; 32 species, 208 reactions: 580 -> 651.
-        if (n <= 256) return take(1, blocks <= 8 ? 4 : 8);
-        if (blocks > 4 * GATHER_BLOCKS) return take(1, 8);
+        if (n <= 128 || (n <= 256 && blocks > 1 && blocks <= 20)) return take(1, blocks <= 8 ? 4 : 8);
+        if (blocks > 4 * GATHER_BLOCKS) return n >= 192 * m.auto_S[mode] && take(1, 8);
         if (n < 3072 || blocks <= 4) return false;
-        const int v = blocks <= 6 ? 2 : blocks <= 9 ? 3 : 4;
+        const int v = grad && n < 16384 ? 4 : blocks <= 6 ? 2 : blocks <= 9 ? 3 : 4;
         return gather_lds(m.gm, GM_ADJ, 1) * (12 / v) <= m.lds_max && take(1, v);
     }
     if (mode == MODE_SRC) {
@@ -173,14 +179,14 @@ static void nominal_shape(const Mechanism& m, int mode, int& S, int& w, int64_t&
     w = m.waves[mode];
     lds = m.lds[mode];
     const int64_t n = 1 << 20;
-    if (m.automatic[mode] ? gather_choice(m, mode, PJ_LAYOUT_C, n, S, w) : gather_takes(m, mode, PJ_LAYOUT_C, n, S, w))
+    if (m.automatic[mode] ? gather_choice(m, mode, PJ_LAYOUT_C, n, true, S, w) : gather_takes(m, mode, PJ_LAYOUT_C, n, S, w))
         lds = gather_lds(m.gm, gather_mode(mode), S);
     else if (m.automatic[mode] ? wide_choice(m, mode, n, S, w) : wide_takes(m, mode, S, w))
         lds = wide_lds(m.gm, w);
 }
 
 // the kernel set of a call of n states and its launch shape
-Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fused) {
+Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fused, bool grad) {
     int S = m.S[mode], w = m.waves[mode];
     bool automatic = m.automatic[mode];
     // a shape that was tuned for the gather kernels is no measure for a call that
@@ -197,7 +203,7 @@ Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fuse
         sw = m.f_waves[mode];
     }
     // (the adjoint with fused source terms: scatter kernels)
-    if (!fused && (automatic ? gather_choice(m, mode, layout, n, S, w) : gather_takes(m, mode, layout, n, S, w)))
+    if (!fused && (automatic ? gather_choice(m, mode, layout, n, grad, S, w) : gather_takes(m, mode, layout, n, S, w)))
         return {KERNEL_GATHER, S, w};
     if (automatic ? wide_choice(m, mode, n, S, w) : wide_takes(m, mode, S, w)) return {KERNEL_WIDE, S, w};
     return {KERNEL_SCATTER, sS, sw};
@@ -295,7 +301,7 @@ pj_status eval(const pj_mech* mech, int mode, pj_form form, pj_layout layout, in
     if (lds > m.lds_max)
         return fail(PJ_E_UNSUPPORTED, "per-state working set (" + std::to_string(lds) +
                                           " B) exceeds the LDS of one workgroup");
-    const pj::Route r = pj::route(m, mode, layout, n, mode == pj::MODE_ADJ && dstate);
+    const pj::Route r = pj::route(m, mode, layout, n, mode == pj::MODE_ADJ && dstate, grad != nullptr);
     if (r.kernel != pj::KERNEL_SCATTER) {
         const pj::GatherCall c{&m.gm, m.d_gm, m.dm.ext, pj::gather_mode(mode), form, layout, r.S, r.waves, n, state, param,
                                dstate, jac, arr, (hipStream_t)stream, vin, grad};

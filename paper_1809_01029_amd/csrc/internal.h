@@ -394,7 +394,7 @@ enum Kernel : int { KERNEL_SCATTER = 0, KERNEL_GATHER = 1, KERNEL_WIDE = 2 };
 struct Route {
     int kernel, S, waves;
 };
-Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fused);
+Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fused, bool grad = true);
 
 // kernels.hip (kernel_body.h)
 enum Mode : int { MODE_SRC = 0, MODE_SPARSE = 1, MODE_DENSE = 2, MODE_ADJ = 3,

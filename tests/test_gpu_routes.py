@@ -186,6 +186,16 @@ def described(name, mech_dir):
     ("gen32", None, "source", "C", 12000, ("scatter", 4, 1)),
     ("gen32", None, "source", "C", 12001, ("wide", 64, 8)),
     ("ns111", None, "source", "C", 20000, ("gather", 2, 4)),
+
+    # adjoints: few states; from where the workgroups' additions weigh less
+    ("ns13", None, "adjoint", "C", 128, ("gather", 1, 4)),
+    ("ns13", None, "adjoint", "C", 129, ("scatter", 4, 1)),
+    ("ns53", None, "adjoint", "C", 256, ("gather", 1, 4)),
+    ("ns53", None, "adjoint", "F", 3072, ("gather", 1, 4)),
+    ("ns53", None, "adjoint", "F", 16383, ("gather", 1, 4)),
+    ("ns53", None, "adjoint", "F", 16384, ("gather", 1, 2)),
+    ("ns360", None, "adjoint", "C", 383, ("scatter", 2, 8)),
+    ("ns360", None, "adjoint", "C", 384, ("gather", 1, 8)),
 ])
 def test_kernel_choice(torch_cuda, api, name, shape, mode, layout, n, want, mech_dir):
     """Both sides of a line: the route, and the results of the path that it takes."""
