@@ -106,18 +106,18 @@ static bool wide_choice(const Mechanism& m, int mode, int64_t n, int& S, int& w)
 
 // The automatic choice between the gather and the scatter kernels for a call
 // of n states, and the gather kernels' shape (false: scatter, in the shape of
-// choose_launch).  Measured on MI355X, scatter -> gather, us per call:
+// choose_launch, or wide).  Measured on MI355X over mechanisms of 13 to 360 species
+// and 64 to 262144 states; scatter -> gather, us per call:
 //   few states: a workgroup per state or two fills the chip sooner; 13 species,
-//     1024 states, sparse 19.5 -> 14.7 (2048: 20.0 -> 18.3, 4096: 20.8 -> 36);
+//     1024 states, sparse 19.8 -> 14.5 (2048: 20.3 -> 18.8, 4096: 21.4 -> 35);
 //     53 species, 100 states, source terms 57 -> 10, sparse 67 -> 16.5;
-//     111 species, 4096 states, source terms 59 -> 34
+//     111 species, 4096 states, source terms 63 -> 35
 //   more than 256 reactions, Jacobians: 53 species, 71199 states, sparse
-//     1388 -> 1110, dense (17799) 408 -> 375; 111 species, 16232 states 752 -> 620
-//     (F 805 -> 716); 360 species, 4096 states 767 -> 660 (F 1270 -> 848)
+//     1388 -> 1110, dense (17799) 408 -> 375; 111 species, 16232 states 752 -> 620;
+//     360 species, 4096 states 767 -> 660 (F 1270 -> 848)
 //   fewer: 20 species, 131072 states, sparse 996 -> 1159
 static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool grad, int& S, int& w) {
     const int blocks = (m.nr + 63) / 64;
-    const bool few = n <= 2048;
     auto take = [&](int s, int v) {
         if (!gather_takes(m, mode, layout, n, s, v)) return false;
         S = s;
@@ -157,18 +157,26 @@ static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_
         if (n > 4096 && blocks <= 4) return false;
         return take(2, blocks <= 9 ? 2 : 4);
     }
+    const bool few = n <= 2048;
     if (!few && blocks <= 4) return false;
-    // layout F: two states write twice as long runs; one if two leave a compute
-    // unit a single workgroup
     if (layout == PJ_LAYOUT_F) {
-        // (sparse, where eight states fit the scatter kernels: 53 species, 65536
-        // states 1200 us against 1545, whose short runs suffer from a power of two
-        // of states; 300007 states 5786 against 5982)
-        if (mode == MODE_SPARSE && !few && m.f_S[mode] == 8) return false;
-        if ((mode == MODE_DENSE || 2 * gather_lds(m.gm, GM_JAC, 2) <= m.lds_max) && take(2, blocks <= 2 * GATHER_BLOCKS ? 4 : 8))
-            return true;
-    } else if (!few && blocks <= 8 && take(2, 4)) {
-        return true;
+        // Two states write twice as long runs; one if two leave a compute unit a
+        // single workgroup.  More waves for more reactions: 60 species, 24001 states,
+        // sparse 543 -> 578 with 4, 499 with 8; 53 species 478 -> 441 with 4.
+        // Where the rows of the output start a multiple of 4 kB apart, neighbouring
+        // rows share a memory channel and short runs suffer (65536 states of 53
+        // species 1200 -> 1545; 16384 of 80 species 571 -> 697, of 111 species
+        // 839 -> 925; dense 8192 of 111 species 667 -> 793): large outputs stay with
+        // the scatter kernels.
+        if (n % 512 == 0) {
+            if (mode == MODE_SPARSE && (n >= 16384 || n * blocks >= 90000)) return false;
+            if (mode == MODE_DENSE && blocks <= 14 && (blocks >= 7 ? n * blocks >= 36000 : blocks == 6 && n >= 16384)) return false;
+        }
+        const int v = blocks <= 6 ? 4 : 8;
+        if ((mode == MODE_DENSE || 2 * gather_lds(m.gm, GM_JAC, 2) <= m.lds_max) && take(2, v)) return true;
+    } else if (blocks <= 6 && (!few || (n > 1536 && blocks >= 5 && (mode == MODE_SPARSE || blocks == 5)))) {
+        // (40 species, 2048 states, sparse 37 -> 31, one state 40)
+        if (take(2, 4)) return true;
     }
     return take(1, blocks <= 4 ? 2 : blocks <= 4 * GATHER_BLOCKS ? 4 : 8);
 }

@@ -196,6 +196,14 @@ def described(name, mech_dir):
     ("ns53", None, "adjoint", "F", 16384, ("gather", 1, 2)),
     ("ns360", None, "adjoint", "C", 383, ("scatter", 2, 8)),
     ("ns360", None, "adjoint", "C", 384, ("gather", 1, 8)),
+
+    # Jacobians: waves by reactions; rows a multiple of 4 kB apart
+    ("gen60", None, "dense", "C", 3000, ("gather", 1, 4)),
+    ("ns53", None, "sparse", "F", 16383, ("gather", 2, 4)),
+    ("ns53", None, "sparse", "F", 16384, ("scatter", 8, 8)),
+    ("gen60", None, "sparse", "F", 3001, ("gather", 2, 8)),
+    ("ns111", None, "dense", "F", 8192, ("scatter", 4, 8)),
+    ("ns111", None, "dense", "F", 8193, ("gather", 2, 8)),
 ])
 def test_kernel_choice(torch_cuda, api, name, shape, mode, layout, n, want, mech_dir):
     """Both sides of a line: the route, and the results of the path that it takes."""
