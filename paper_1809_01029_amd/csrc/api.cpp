@@ -206,7 +206,7 @@ Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fuse
         w = m.auto_waves[mode];
     }
     int sS = S, sw = w;              // the scatter kernels' shape
-    if (automatic && layout == PJ_LAYOUT_F && (n > 2048 || m.f_S[mode] == sS)) {
+    if (automatic && layout == PJ_LAYOUT_F && n >= m.f_from[mode]) {
         sS = m.f_S[mode];
         sw = m.f_waves[mode];
     }
@@ -246,19 +246,22 @@ void choose_launch(Mechanism& m) {
         m.auto_S[mode] = S;
         m.auto_waves[mode] = default_waves(m, mode, S, gr);
         m.tuned_layout[mode] = -1;
-        // Jacobians in layout F: 8 states write 64 bytes of a value together
-        // (sparse, 4 -> 8 states, us: 13 species, 131072 states 346 -> 275; 20
-        // species 948 -> 894; 53 species, 65536 states 1284 -> 1200, 300007 states
-        // 5964 -> 5786); dense, a state per workgroup: with 8 waves the rows of
-        // 2048 states meet in the same channels (360 species 2759 us, 7 waves
-        // 2635; 2047 states 1851 and 1826)
+        // Jacobians in layout F: 8 states write 64 bytes of a value together, once
+        // their workgroups fill the chip (f_from, at most 8 a unit) and where 4 states don't run on one
+        // wave, whose additions have a fixed order, and 8 on more.  Sparse, 4 -> 8
+        // states, us: 13 species, 12001 states 42 -> 60, 32768 88 -> 72, 131072 333 -> 271;
+        // 32 species, 3000 states 77 -> 81, 20000 223 -> 222, 65536 710 -> 684; dense, 13
+        // species, 32768 states 110 -> 80, 32 species 476 -> 405 (8 states have 8 map
+        // reads in flight, the other kernels 16)
         m.f_S[mode] = m.auto_S[mode];
         m.f_waves[mode] = m.auto_waves[mode];
+        m.f_from[mode] = 0;
         if ((mode == MODE_SPARSE || mode == MODE_DENSE) && !m.dm.det && !m.dm.lsearch) {
             const int w8 = default_waves(m, mode, 8, gr);
-            if (S == 4 && L(8, w8) <= m.lds_max) {
+            if (S == 4 && L(8, w8) <= m.lds_max && (w8 == 1 || m.auto_waves[mode] > 1)) {
                 m.f_S[mode] = 8;
                 m.f_waves[mode] = w8;
+                m.f_from[mode] = 256 * 8 * std::min<int64_t>(8, m.lds_max / L(8, w8));
             } else if (mode == MODE_DENSE && S == 1 && m.f_waves[mode] == 8) {
                 m.f_waves[mode] = 7;
             }
@@ -692,6 +695,7 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
         m.auto_waves[mode] = scatter_w;
         m.f_S[mode] = scatter_S;
         m.f_waves[mode] = scatter_w;
+        m.f_from[mode] = 0;
     }
     m.S[mode] = best_S;
     m.waves[mode] = best_w;

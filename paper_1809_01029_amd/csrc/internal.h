@@ -307,7 +307,8 @@ struct Mechanism {
     bool automatic[4] = {};          // the mode's launch shape is the automatic one
     int tuned_layout[4] = {-1, -1, -1, -1};   // the layout it was tuned in, if the gather kernels won
     int auto_S[4] = {1, 1, 1, 1}, auto_waves[4] = {1, 1, 1, 1};   // the scatter kernels' automatic shape,
-    int f_S[4] = {1, 1, 1, 1}, f_waves[4] = {1, 1, 1, 1};         // and in layout F (8 states: of more than 2048)
+    int f_S[4] = {1, 1, 1, 1}, f_waves[4] = {1, 1, 1, 1};         // and in layout F of f_from states or more
+    int64_t f_from[4] = {0, 0, 0, 0};
     // gather kernels: tables and the host copy of the reaction records with its
     // byte offset (Arrhenius parameters)
     GatherMech gm{};

@@ -204,6 +204,13 @@ def described(name, mech_dir):
     ("gen60", None, "sparse", "F", 3001, ("gather", 2, 8)),
     ("ns111", None, "dense", "F", 8192, ("scatter", 4, 8)),
     ("ns111", None, "dense", "F", 8193, ("gather", 2, 8)),
+
+    # layout F: 8 states only in launches that fill the chip, and not where 4 run
+    # on one wave (whose additions have a fixed order) and 8 don't
+    ("ns13", None, "sparse", "F", 16383, ("scatter", 4, 1)),
+    ("ns13", None, "sparse", "F", 16384, ("scatter", 8, 1)),
+    ("gen20", None, "sparse", "F", 40000, ("scatter", 4, 1)),
+    ("gen20", None, "dense", "F", 40000, ("scatter", 4, 1)),
 ])
 def test_kernel_choice(torch_cuda, api, name, shape, mode, layout, n, want, mech_dir):
     """Both sides of a line: the route, and the results of the path that it takes."""
