@@ -206,9 +206,15 @@ Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fuse
         w = m.auto_waves[mode];
     }
     int sS = S, sw = w;              // the scatter kernels' shape
-    if (automatic && layout == PJ_LAYOUT_F && n >= m.f_from[mode]) {
-        sS = m.f_S[mode];
-        sw = m.f_waves[mode];
+    if (automatic && layout == PJ_LAYOUT_F) {
+        if (n >= m.f_from[mode]) {
+            sS = m.f_S[mode];
+            sw = m.f_waves[mode];
+        }
+        // dense, a state per workgroup, rows a multiple of 4 kB apart: with 8 waves
+        // they meet in the same channels (360 species, 1024 states 1143 us, 7 waves 773,
+        // 2048 states 2788 and 2576; 1500 states 1259 and 1287)
+        if (mode == MODE_DENSE && sS == 1 && sw == 8 && n % 512 == 0) sw = 7;
     }
     // (the adjoint with fused source terms: scatter kernels)
     if (!fused && (automatic ? gather_choice(m, mode, layout, n, grad, S, w) : gather_takes(m, mode, layout, n, S, w)))
@@ -262,8 +268,6 @@ void choose_launch(Mechanism& m) {
                 m.f_S[mode] = 8;
                 m.f_waves[mode] = w8;
                 m.f_from[mode] = 256 * 8 * std::min<int64_t>(8, m.lds_max / L(8, w8));
-            } else if (mode == MODE_DENSE && S == 1 && m.f_waves[mode] == 8) {
-                m.f_waves[mode] = 7;
             }
         }
         const int maxS = max_states(kernel_mode(m, mode, false));

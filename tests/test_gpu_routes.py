@@ -211,6 +211,10 @@ def described(name, mech_dir):
     ("ns13", None, "sparse", "F", 16384, ("scatter", 8, 1)),
     ("gen20", None, "sparse", "F", 40000, ("scatter", 4, 1)),
     ("gen20", None, "dense", "F", 40000, ("scatter", 4, 1)),
+
+    # one state a workgroup, dense: 7 waves where the rows meet in the same channels
+    ("ns360", None, "dense", "F", 1024, ("scatter", 1, 7)),
+    ("ns360", None, "dense", "F", 1025, ("scatter", 1, 8)),
 ])
 def test_kernel_choice(torch_cuda, api, name, shape, mode, layout, n, want, mech_dir):
     """Both sides of a line: the route, and the results of the path that it takes."""
