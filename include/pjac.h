@@ -241,9 +241,9 @@ pj_status pj_mech_get_arrhenius(const pj_mech* mech, double* lnA, double* b, dou
  * per workgroup is the paper's deep mapping (Sec. 2.1: the lanes of a
  * workgroup cooperate on one state), 64 states on one wave its shallow
  * mapping (a lane per state).  0 restores the automatic choice, which
- * depends on the call's states and layout: few states and, for Jacobians,
- * mechanisms of more than 256 reactions take one or two states per workgroup;
- * source terms of many states take 64, or two of large mechanisms;
+ * depends on the call's states and layout (pj_mech_kernel): few states and, for
+ * Jacobians, mechanisms of more than 256 reactions mostly take one or two states
+ * per workgroup; source terms of many states take 64, or two of large mechanisms;
  * the others the most states, up to 4 (8 in layout F), whose working set fits
  * the LDS of one workgroup, and enough waves for about 8 resident waves per compute unit.  A
  * states_per_group that does not fit for a mode is ignored for that mode.
@@ -307,9 +307,10 @@ int pj_mech_dense_unroll(const pj_mech* mech);
  * 2) and are overwritten.  Every shape runs one warm-up launch and `reps`
  * (>= 1) timed launches on `stream`; the call synchronises the stream.  On
  * success the chosen shape and its mean time per launch (ms) are stored
- * through the pointers that are not NULL.  Where it is one of one or two
- * states, calls in the other layout (and adjoints with fused source terms) take
- * the automatic choice.  Errors as for the evaluation
+ * through the pointers that are not NULL.  It stands for calls in that layout
+ * (source terms of the wide kernel: in both); those in the other layout, and
+ * adjoints with fused source terms where the gather kernels won, take the
+ * automatic choice.  Errors as for the evaluation
  * calls; PJ_E_INVALID also for a bad mode, reps < 1 or n_states < 1.
  */
 pj_status pj_mech_autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int64_t n_states,

@@ -181,26 +181,19 @@ static bool gather_choice(const Mechanism& m, int mode, pj_layout layout, int64_
     return take(1, blocks <= 4 ? 2 : blocks <= 4 * GATHER_BLOCKS ? 4 : 8);
 }
 
-// the shape of a large call in layout C
-static void nominal_shape(const Mechanism& m, int mode, int& S, int& w, int64_t& lds) {
-    S = m.S[mode];
-    w = m.waves[mode];
-    lds = m.lds[mode];
-    const int64_t n = 1 << 20;
-    if (m.automatic[mode] ? gather_choice(m, mode, PJ_LAYOUT_C, n, true, S, w) : gather_takes(m, mode, PJ_LAYOUT_C, n, S, w))
-        lds = gather_lds(m.gm, gather_mode(mode), S);
-    else if (m.automatic[mode] ? wide_choice(m, mode, n, S, w) : wide_takes(m, mode, S, w))
-        lds = wide_lds(m.gm, w);
-}
-
 // the kernel set of a call of n states and its launch shape
 Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fused, bool grad) {
     int S = m.S[mode], w = m.waves[mode];
     bool automatic = m.automatic[mode];
-    // a shape that was tuned for the gather kernels is no measure for a call that
-    // they don't take, nor for the other layout (111 species, 262144 states, the
-    // shape of layout C in layout F: 18.7 ms, the automatic one 13.1)
-    if (m.tuned_layout[mode] >= 0 && (m.tuned_layout[mode] != layout || fused || !gather_takes(m, mode, layout, n, S, w))) {
+    // A tuned shape is no measure for the other layout (111 species, 262144 states,
+    // the gather kernels' shape of layout C in layout F: 18.7 ms, the automatic one
+    // 13.1), except the wide kernel's, which stages either; nor is the gather kernels' for a call that they don't take.
+    if (m.tuned_layout[mode] >= 0) {
+        if (m.tuned_kernel[mode] == KERNEL_WIDE && wide_takes(m, mode, S, w)) return {KERNEL_WIDE, S, w};
+        if (m.tuned_layout[mode] == layout) {
+            if (m.tuned_kernel[mode] == KERNEL_SCATTER) return {KERNEL_SCATTER, S, w};
+            if (!fused && gather_takes(m, mode, layout, n, S, w)) return {KERNEL_GATHER, S, w};
+        }
         automatic = true;
         S = m.auto_S[mode];
         w = m.auto_waves[mode];
@@ -221,6 +214,15 @@ Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fuse
         return {KERNEL_GATHER, S, w};
     if (automatic ? wide_choice(m, mode, n, S, w) : wide_takes(m, mode, S, w)) return {KERNEL_WIDE, S, w};
     return {KERNEL_SCATTER, sS, sw};
+}
+
+// the shape of a large call in layout C (as tuned, if it is)
+static void nominal_shape(const Mechanism& m, int mode, int& S, int& w, int64_t& lds) {
+    const pj_layout layout = m.tuned_layout[mode] >= 0 ? (pj_layout)m.tuned_layout[mode] : PJ_LAYOUT_C;
+    const Route r = route(m, mode, layout, 1 << 20, false);
+    S = r.kernel == KERNEL_SCATTER ? m.S[mode] : r.S;
+    w = r.kernel == KERNEL_SCATTER ? m.waves[mode] : r.waves;
+    lds = r.kernel == KERNEL_SCATTER ? m.lds[mode] : r.kernel == KERNEL_GATHER ? gather_lds(m.gm, gather_mode(mode), S) : wide_lds(m.gm, w);
 }
 
 // Waves per workgroup for S states per workgroup: enough that a compute unit
@@ -692,7 +694,10 @@ pj_status autotune(pj_mech* mech, int mode, pj_form form, pj_layout layout, int6
     (void)hipEventDestroy(e1);
     if (!err.empty()) return fail(PJ_E_DEVICE, err);
     m.automatic[mode] = false;
-    m.tuned_layout[mode] = pj::gather_takes(m, mode, layout, n_states, best_S, best_w) ? layout : -1;
+    m.tuned_layout[mode] = layout;
+    m.tuned_kernel[mode] = pj::gather_takes(m, mode, layout, n_states, best_S, best_w) ? pj::KERNEL_GATHER
+                           : pj::wide_takes(m, mode, best_S, best_w)                   ? pj::KERNEL_WIDE
+                                                                                       : pj::KERNEL_SCATTER;
     if (mode == pj::MODE_ADJ) {
         // calls with fused source terms stay with the scatter kernels
         m.auto_S[mode] = scatter_S;

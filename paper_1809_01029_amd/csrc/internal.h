@@ -305,7 +305,8 @@ struct Mechanism {
     int user_S = 0, user_waves = 0;        // 0 = automatic
     int dense_unroll = 16;                 // dense output: map entries in flight per lane (8 or 16)
     bool automatic[4] = {};          // the mode's launch shape is the automatic one
-    int tuned_layout[4] = {-1, -1, -1, -1};   // the layout it was tuned in, if the gather kernels won
+    int tuned_layout[4] = {-1, -1, -1, -1};   // the layout it was tuned in,
+    int tuned_kernel[4] = {0, 0, 0, 0};       // and the Kernel that won
     int auto_S[4] = {1, 1, 1, 1}, auto_waves[4] = {1, 1, 1, 1};   // the scatter kernels' automatic shape,
     int f_S[4] = {1, 1, 1, 1}, f_waves[4] = {1, 1, 1, 1};         // and in layout F of f_from states or more
     int64_t f_from[4] = {0, 0, 0, 0};

@@ -246,3 +246,19 @@ def test_kernel_choice(torch_cuda, api, name, shape, mode, layout, n, want, mech
         else:
             J = api.dense_as_sij(api.eval_jacobian_dense(mech, xs, ps, "conp", layout), layout)[ti].cpu().numpy()
         check_jac(J, J_o, J_b, what)
+
+
+# (13 species, sparse, layout F: shapes of 8 and more states of the scatter kernels win)
+@pytest.mark.parametrize("name,mode,n", [("ns13", "sparse", 32768), ("ns13", "dense", 32768), ("ns53", "sparse", 3000),
+                                         ("ns53", "source", 40000)])
+@pytest.mark.parametrize("layout,other", [("F", "C"), ("C", "F")])
+def test_tuned_shape_stands_for_its_layout(torch_cuda, api, name, mode, n, layout, other, mech_dir):
+    """A tuned shape is the one of calls in its layout, whichever kernels won; the
+    other layout keeps the automatic choice (the wide kernel stages either)."""
+    torch = torch_cuda
+    sg = Segment(torch, api, mech_dir, name, n, mode, layout, 12)
+    auto = sg.mech.kernel(mode, other, n)
+    S, W, _ = api.autotune(sg.mech, sg.xs, sg.ps, "conp", layout, mode=mode, reps=3)
+    own = sg.mech.kernel(mode, layout, n)
+    assert own[1:] == (S, W) and sg.mech.launch_shape(api.MODES[mode]) == (S, W)
+    assert sg.mech.kernel(mode, other, n) == (own if own[0] == "wide" else auto)
