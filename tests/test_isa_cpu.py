@@ -125,3 +125,35 @@ def test_no_barrier_with_pending_lds_store(tmp_path):
     bad, nbar = pending_lds_barriers(asm)
     assert nbar > 10, "expected the kernels' barriers in the assembly"
     assert bad == [], f"barriers reached with LDS stores in flight at assembly lines {bad}"
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC), reason="hipcc not found")
+@pytest.mark.parametrize("ext", ["false", "true"])
+@pytest.mark.parametrize("head,kernels", [
+    ("gather_body.h", ["pj_gather_kernel<PJ_CONP, PJ_LAYOUT_C, GM_SRC, 1, {ext}>",
+                       "pj_gather_kernel<PJ_CONP, PJ_LAYOUT_F, GM_SRC, 2, {ext}>",
+                       "pj_gather_kernel<PJ_CONV, PJ_LAYOUT_C, GM_JAC, 1, {ext}>",
+                       "pj_gather_kernel<PJ_CONP, PJ_LAYOUT_F, GM_JAC, 2, {ext}>",
+                       "pj_gather_kernel<PJ_CONP, PJ_LAYOUT_C, GM_DENSE, 1, {ext}>",
+                       "pj_gather_kernel<PJ_CONP, PJ_LAYOUT_F, GM_DENSE, 2, {ext}>",
+                       "pj_gather_adjoint<PJ_CONP, PJ_LAYOUT_C, {ext}>"]),
+    ("wide_body.h", ["pj_wide_source<PJ_CONP, PJ_LAYOUT_C, 8, {ext}>",
+                     "pj_wide_source<PJ_CONV, PJ_LAYOUT_F, 16, {ext}>"]),
+])
+def test_no_barrier_with_pending_lds_store_fixed_order_kernels(tmp_path, head, kernels, ext):
+    """The gather and wide kernels, with the flags that the library builds them with."""
+    from paper_1809_01029_amd import build
+    # a pointer to an instantiation, so that no signature is written out here
+    src = f'#include "{head}"\nnamespace pj {{\n' + "".join(
+        f"void* keep{k}() {{ return (void*)&{name.format(ext=ext)}; }}\n" for k, name in enumerate(kernels)) + "}\n"
+    f, out = tmp_path / "isa_check.hip", tmp_path / "isa_check.s"
+    f.write_text(src)
+    subprocess.run([HIPCC, "-O3", "-std=c++17", "-I", os.path.join(ROOT, "include"), "-I", CSRC] + build.DEVICE +
+                   build.GATHER + ["--offload-device-only", "-S", str(f), "-o", str(out)],
+                   check=True, capture_output=True, timeout=600)
+    asm = out.read_text()
+    names = set(re.findall(r"^\s*\.amdhsa_kernel\s+(\S+)", asm, re.M))
+    assert len(names) == len(kernels), sorted(names)
+    bad, nbar = pending_lds_barriers(asm)
+    assert nbar >= 2 * len(kernels), "expected the kernels' barriers in the assembly"
+    assert bad == [], f"barriers reached with LDS stores in flight at assembly lines {bad}"
