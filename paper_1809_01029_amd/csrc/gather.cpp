@@ -193,7 +193,8 @@ void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std:
         for (auto& e : r.prod) b += e.second;
         if (a > MAXSIDE || b > MAXSIDE) return;
     }
-    if (nr < 1 || nr >= 8192 || (nr + 63) / 64 > 8 * GATHER_BLOCKS || ns >= 8192) return;
+    // (8 waves of GATHER_BLOCKS blocks: 2560 reactions; the lists' 13 bits hold 8191)
+    if (nr < 1 || (nr + 63) / 64 > 8 * GATHER_BLOCKS || ns >= 8192) return;
     const bool approx = (m.opts & PJ_OPT_APPROX_JACOBIAN) != 0;
     const int nr_pad = (int)rec.size();
     // The kernel order of rec by class and shape, its classes the costliest
@@ -339,10 +340,6 @@ void build_gather(const Mechanism& m, const std::vector<RxnRec>& rec, const std:
             dense_of[dense_rows[d]] = (int)br.size();
             br.push_back({(uint32_t)d, {}});
         }
-    struct Entry {
-        uint32_t meta;
-        std::vector<uint32_t> c;
-    };
     std::vector<std::vector<uint32_t>> ent(m.nnz);
     for (int p = 0; p < nr; ++p) {
         for (auto& d : deps[p]) col[d.species].c.push_back((d.elem << 3 | (d.minus ? 1u : 0u)) | (uint32_t)p << 16 | (uint32_t)dom[p] << 29);

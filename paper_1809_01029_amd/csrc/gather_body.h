@@ -11,7 +11,7 @@
 //
 //   pool   F_i = c_i kf_i prod C, B_i = c_i kr_i prod C (the two one-way rates
 //          of progress), T_ik = Q_M,i (alpha_ik - 1) C_k of its third bodies,
-//          q_i, dq_i/dT, dq_i/dS, dE_i, dOmega_i
+//          q_i, dq_i/dT, dq_i/dS, dE_i
 //   rows   d wdot_k / d[C]_j = 1/[C]_j (sum nu_ki (nu'_ij F_i - nu''_ij B_i) + sum nu_ki T_ij)
 //
 // since dq/d[C]_j of a mass-action rate is its order times the rate over
@@ -339,6 +339,7 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
     extern __shared__ double lds[];
     typedef double V __attribute__((ext_vector_type(NV)));
     constexpr bool JAC = MODE == GM_JAC || MODE == GM_DENSE, dense = MODE == GM_DENSE, ADJ = MODE == GM_ADJ;
+    static_assert(!ADJ || NV == 1, "an adjoint's workgroup holds one state");
     constexpr bool DER = MODE != GM_SRC;
     constexpr int RB = GATHER_BLOCKS;    // most blocks of reactions of a wave
     constexpr int layout = LAYOUT;
@@ -557,15 +558,13 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
         for (int k = lane; k < ns; k += 64) d0 += SP(k, A_C) * SP(k, A_CP);
         const V Dp = vmap(d0, [](double x) { return wave_total(x); });
         if (wave == 0 && lane == 0) vec(SC, SC_DP) = Dp;
-        for (int it = tid; it < ns * NV; it += nthr) {
-            const int k = NV == 1 ? it : it / NV, v = NV == 1 ? 0 : it - k * NV;
-            auto C_ = [&](int q) { return SC[q * NV + v]; };
-            const double T = C_(SC_T), Vv = C_(SC_V), P = C_(SC_P), vT = C_(SC_VT), vS = C_(SC_VS);
-            const double a = -(vT + vS * (FORM == PJ_CONP ? Vv : P) * C_(SC_INVT)) / (NV == 1 ? Dp[0] : Dp[v]);
+        for (int k = tid; k < ns; k += nthr) {
+            const double T = SC[SC_T], Vv = SC[SC_V], P = SC[SC_P], vT = SC[SC_VT], vS = SC[SC_VS];
+            const double a = -(vT + vS * (FORM == PJ_CONP ? Vv : P) * SC[SC_INVT]) / Dp[0];
             const double b = vS * RU * T * (FORM == PJ_CONP ? Vv / P : 1.0);
-            const double h = A[fld(k, A_H) * NV + v];
-            A[fld(k, A_Y) * NV + v] = Vv * A[fld(k, A_VV) * NV + v] + (a * T) * (FORM == PJ_CONP ? h : h - 1.0) + b * at(gm->wfac, (uint32_t)k);
-            if (k == 0) SC[SC_KAP * NV + v] = a;
+            const double h = A[fld(k, A_H)];
+            A[fld(k, A_Y)] = Vv * A[fld(k, A_VV)] + (a * T) * (FORM == PJ_CONP ? h : h - 1.0) + b * at(gm->wfac, (uint32_t)k);
+            if (k == 0) SC[SC_KAP] = a;
         }
         __syncthreads();
     }
@@ -987,18 +986,11 @@ __device__ __forceinline__ void gather_group(GatherPtr gmp, const long n,
             if (first) SP(what, A_E) = w0 / vclamp(SP(what, A_C));
         }
         __syncthreads();
-        const int G = nthr / NV;
-        const int s2 = NV == 1 ? 0 : layout == PJ_LAYOUT_F ? tid % NV : tid / G;
-        const int g2 = NV == 1 ? tid : layout == PJ_LAYOUT_F ? tid / NV : tid - s2 * G;
-        const long st2 = qg * NV + s2;
-        if (st2 < n) {
-            auto C_ = [&](int q) { return SC[q * NV + s2]; };
-            const double lb = C_(SC_LB), kt = C_(SC_KAP), cpb = C_(SC_CB), iV = C_(SC_INVV);
-            for (int i = g2; i < N; i += G) {
-                const double y = i == 0 ? C_(SC_TT) : i == 1 ? C_(SC_TS) : iV * (A[fld(i - 2, A_E)] - lb) + kt * (A[fld(i - 2, A_CP)] - cpb);
-                if (layout == PJ_LAYOUT_F) jac[(long)i * n + st2] = y;
-                else jac[st2 * (long)N + i] = y;
-            }
+        const double lb = SC[SC_LB], kt = SC[SC_KAP], cpb = SC[SC_CB], iV = SC[SC_INVV];
+        for (int i = tid; i < N; i += nthr) {
+            const double y = i == 0 ? SC[SC_TT] : i == 1 ? SC[SC_TS] : iV * (A[fld(i - 2, A_E)] - lb) + kt * (A[fld(i - 2, A_CP)] - cpb);
+            if (layout == PJ_LAYOUT_F) jac[(long)i * n + qg] = y;
+            else jac[qg * (long)N + i] = y;
         }
         return;
     }

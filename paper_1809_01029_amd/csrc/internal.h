@@ -192,8 +192,8 @@ constexpr uint32_t CHUNK_PRESSURE = 1u << 15;
 // A set of sums whose lists are cut into groups of 64 lanes.  Every lane has
 // three words of contributions in its head and four in its ext, both found
 // from the group's index alone (loads that nothing waits for), and more in
-// chunks of four words.  A sum takes 2^k neighbouring lanes, the same for all
-// sums of a group.
+// chunks of four words.  A sum takes some 2^j neighbouring lanes, at most the
+// 2^k of its group's descriptor.
 struct SumLists {
     int n;                           // groups
     int pad;
