@@ -277,7 +277,9 @@ int pj_mech_launch_shape(const pj_mech* mech, int mode, int* states_per_group, i
  * (one or two states per workgroup, fixed order), 2 the wide kernel (source
  * terms, a lane per state; *waves_per_group counts pairs of waves), and its
  * shape through the pointers that are not NULL.  fused: non-zero for an
- * adjoint with source terms.  -1 for a NULL or not uploaded mechanism, a bad
+ * adjoint with source terms; an adjoint is taken to ask for its parameter sums
+ * (without them 5 to 9 blocks of 64 reactions take fewer waves below 16384
+ * states).  -1 for a NULL or not uploaded mechanism, a bad
  * mode, layout or n_states.
  */
 int pj_mech_kernel(const pj_mech* mech, int mode, pj_layout layout, int64_t n_states, int fused, int* states_per_group,
@@ -288,7 +290,8 @@ int pj_mech_kernel(const pj_mech* mech, int mode, pj_layout layout, int64_t n_st
  * the entries it writes with `entries` reads in flight per lane: 16 (the
  * default; 0 selects it) pays where a lane writes many entries, 8 where it
  * writes few (small mechanisms, many states per workgroup); 16 applies at up
- * to 4 states per workgroup, larger shapes read 8.  The autotuner of mode 2
+ * to 4 states per workgroup, larger shapes read 8, and it has no effect where the
+ * gather kernels run (pj_mech_kernel).  The autotuner of mode 2
  * chooses it with the shape.  The values are identical either way.
  * PJ_E_INVALID for NULL or another value; pj_mech_dense_unroll: the current
  * choice, -1 for NULL.

@@ -187,7 +187,8 @@ Route route(const Mechanism& m, int mode, pj_layout layout, int64_t n, bool fuse
     bool automatic = m.automatic[mode];
     // A tuned shape is no measure for the other layout (111 species, 262144 states,
     // the gather kernels' shape of layout C in layout F: 18.7 ms, the automatic one
-    // 13.1), except the wide kernel's, which stages either; nor is the gather kernels' for a call that they don't take.
+    // 13.1), except the wide kernel's, which stages either; nor is the gather
+    // kernels' for a call that they don't take.
     if (m.tuned_layout[mode] >= 0) {
         if (m.tuned_kernel[mode] == KERNEL_WIDE && wide_takes(m, mode, S, w)) return {KERNEL_WIDE, S, w};
         if (m.tuned_layout[mode] == layout) {

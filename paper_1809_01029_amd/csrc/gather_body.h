@@ -45,10 +45,10 @@
 // coalesced.
 //
 // Sparse Jacobian of 111 species and 784 reactions, CONP, layout C, 262144
-// states: 8.35 ms against the scatter kernels' 11.21 (4 states and 8 waves a
-// workgroup, the best of their shapes).  About 13,500 vector instructions a
-// state, 70% of the issue slots of the four SIMDs: list words decoded, reads and
-// additions are 60% of them, the reactions 30%; LDS reads take 43% of the compute
+// states: 8.26 ms against the scatter kernels' 11.21 (4 states and 8 waves a
+// workgroup, the best of their shapes).  14,100 vector instructions a
+// state, 74% of the issue slots of the four SIMDs: list words decoded, reads and
+// additions are about 60% of them, the reactions 30%; LDS reads take 44% of the compute
 // unit's time, bank conflicts 45% of that.  Writing the output alone takes 1.4
 // ms at the fill rate.  Four waves a state: the 40 kB of a state let four
 // workgroups share a compute unit, which at 128 registers is all the waves it
@@ -1413,8 +1413,8 @@ pj_gather_kernel(const GatherMech* const gmp, const long n, const long ngroups, 
 // partial to three accumulators.  Persistent workgroups, which sum their
 // states' parameter derivatives in LDS (each element has one lane) and add them
 // to the output once.  111 species, 784 reactions, 65536 states: 1.47 ms
-// against 1.80 (scatter, 4 states and 4 waves); 7,600 vector instructions a
-// state, 62% of the issue slots at 12 waves a compute unit.  At 128 registers
+// against 1.80 (scatter, 4 states and 4 waves); 6,900 vector instructions a
+// state, 52% of the issue slots at 12 waves a compute unit.  At 128 registers
 // (16 waves) 66 spilled ones made it 2.46 ms.
 template <int FORM, int LAYOUT, bool EXT>
 __global__ void __launch_bounds__(MAX_THREADS) __attribute__((amdgpu_waves_per_eu(PJ_WPE_ADJ)))
