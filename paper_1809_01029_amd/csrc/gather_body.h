@@ -52,7 +52,7 @@
 // unit's time, bank conflicts 45% of that.  Writing the output alone takes 1.4
 // ms at the fill rate.  Four waves a state: the 40 kB of a state let four
 // workgroups share a compute unit, which at 128 registers is all the waves it
-// holds (3 waves 10.1 ms, 8 waves 12.6; two states with 8 waves 9.2).  Lists
+// holds (3 waves 9.5 ms, 8 waves 11.3; two states with 8 waves 8.3).  Lists
 // sorted so that all lanes of a group add or subtract together save a tenth of
 // the instructions, but what they are padded with costs more reads: 8.9 ms.
 #pragma once
